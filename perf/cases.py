@@ -134,7 +134,8 @@ def _weights(kind, rows, col, seed):
     if kind == "unit":
         return torch.ones(col.numel(), dtype=torch.float64, device=col.device)
     a, b = torch.minimum(rows, col).long(), torch.maximum(rows, col).long()
-    h = _mix(_mix((a << 32) | b) ^ (seed * 0x9E3779B1 + 12345))
+    fold = (seed * 0x9E3779B1 + 12345) & ((1 << 64) - 1)
+    h = _mix(_mix((a << 32) | b) ^ (fold - (1 << 64) if fold >> 63 else fold))
     if kind == "int":
         return ((h >> 20) & 7).double() + 1.0
     return 0.5 + ((h >> 12) & ((1 << 40) - 1)).double() * 2.0 ** -40
