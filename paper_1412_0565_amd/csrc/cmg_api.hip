@@ -21,6 +21,7 @@
 
 #include "cmg.h"
 #include "cmg_internal.h"
+#include "jump.h"
 
 using namespace cmg;
 
@@ -82,6 +83,9 @@ struct HostLevel {
     int32_t* fpart = nullptr;  // ... and its row split
     int fbgrid = 0;            // persistent level: workgroups of its step-mode fallback
     int32_t* fbpart = nullptr; // ... and their row split
+    double* jsum = nullptr;    // FP64 levels: jumps over many PI steps (LevelDev)
+    double* jback = nullptr;
+    double* jmom = nullptr;
     int lmin = 0x7fffffff;     // rows traversal: rows with more entries are long
     int32_t* lrows = nullptr;  // ... their count and the list (nullptr: none)
     int k = 0;
@@ -869,6 +873,9 @@ LevelDev level_dev(const HostLevel& L) {
     d.wk = L.wk;
     d.lmin = L.lrows ? L.lmin : 0x7fffffff;
     d.lrows = L.lrows;
+    d.jsum = L.jsum;
+    d.jback = L.jback;
+    d.jmom = L.jmom;
     return d;
 }
 
@@ -1282,12 +1289,27 @@ cmg_status build_refine_plan(cmg_ctx* c) {
         ALLOC(c->d_step, StepJob, J + 1);
         ALLOC(c->d_step_fb, StepJob, J + 1);
     }
+    // Jumps over many PI steps (jump.h) on FP64 levels.  Levels are refined
+    // one after the other and the output vector is written after the last,
+    // so its buffer holds the two vectors of a jump (twice level 0's entries
+    // where level 0 can jump itself; coarser levels fit the first half, two
+    // heavy edge matching levels excepted).
+    const int32_t n0 = c->lv[0].n;
+    const int64_t ny = (c->lv[0].fp32 ? 1 : 2) * (int64_t)n0;
+    ALLOC(c->d_y, double, ny);
+    double* jmom = nullptr;
+    ALLOC(jmom, double, kJumpWords);
+    for (int j = 0; j <= top; ++j) {
+        HostLevel& L = c->lv[j];
+        if (L.fp32 || 2 * (int64_t)L.n > ny) continue;
+        L.jsum = c->d_y;
+        L.jback = c->d_y + L.n;
+        L.jmom = jmom;
+    }
     std::vector<LevelDev> ld(J + 1);
     for (int j = 0; j <= J; ++j) ld[j] = level_dev(c->lv[j]);
     ALLOC(c->d_lv, LevelDev, J + 1);
     CK(hipMemcpyAsync(c->d_lv, ld.data(), sizeof(LevelDev) * (J + 1), hipMemcpyHostToDevice, c->stream));
-    const int32_t n0 = c->lv[0].n;
-    ALLOC(c->d_y, double, n0);
     if (c->lv[0].fp32 && o.fp64_final_sweeps > 0) {
         ALLOC(c->d_fa, double, n0);
         ALLOC(c->d_fb, double, 8);
@@ -1627,7 +1649,9 @@ cmg_status run_step_level(cmg_ctx* c, int j, hipStream_t s, bool fallback = fals
     const StepJob* job = (fb ? c->d_step_fb : c->d_step) + j;
     const int grid = fb ? L.fbgrid : L.grid;
     const int kind = job_kind(L.variant, L.lanes, L.fp32, L.wk);
-    const int maxit = c->opt.max_iters_per_level;
+    // launches: a step each, except that a jump over many steps takes a few
+    // launches of its own, more if it is taken back
+    const int maxit = (int)std::min<int64_t>(2 * (int64_t)c->opt.max_iters_per_level + 1024, 0x7fffffff);
     CK(launch_step_begin(job, grid, kind, s));
     if (L.kfix > 0) {  // fixed schedule: the step count is known, no host checks
         for (int i = 0; i < L.kfix; ++i) CK(launch_step_pi(job, grid, kind, s));

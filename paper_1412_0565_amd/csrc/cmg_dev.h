@@ -218,6 +218,9 @@ struct LevelDev {
     int32_t ileave;      // rows traversal of the persistent grid kernel: 1 if each workgroup's PI
                          // steps take row chunks interleaved over its XCD's workgroups (the
                          // long rows stay with its own part); never staged in LDS
+    double* jsum;        // FP64 levels that may jump over PI steps: the jump's sum (n entries),
+    double* jback;       // ... the vector before it (n entries)
+    double* jmom;        // ... and its moments (kJumpWords entries); nullptr: no jumps
 };
 
 // State a refinement launch leaves for the next level (device written).
@@ -306,6 +309,14 @@ struct StepCtl {
     double pmu, ps;       // the same for the previous vector
     double utv;
     int32_t k, cur, done, hit;
+    // Jumps over many steps (jump.h).  The next launch is a plain step
+    // (mode 0), a product of a jump (1 the first, 2 another), the copy (3)
+    // and the sum of squares (4) of a jump that was kept, or the copy back
+    // of one that was not (5).
+    int32_t mode, j, K, d;        // products done, steps and products of the jump
+    int32_t since, hold, more;    // plain steps since the last jump, to hold, steps to jump next
+    double cj;                    // coefficient of the next product's vector
+    double utvp, r;               // (u, v) of the step before; ||B v|| / g of the last plain step
 };
 
 // One large level refined step by step.

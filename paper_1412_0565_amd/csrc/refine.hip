@@ -15,6 +15,7 @@
 #include <mutex>
 
 #include "cmg_internal.h"
+#include "jump.h"
 
 namespace cmg {
 
@@ -517,17 +518,33 @@ __device__ __forceinline__ void step_sum4(double (&v)[4], double* red, int& pari
     }
 }
 
-// One PI step of a small level, rows shared by `nthr` threads in G-lane
-// groups.  Pointers are either all LDS (staged modes) or all global.
-template <int G, bool W32, bool C16, bool LDS>
+// A product of a jump on a single-workgroup level, as in JumpOp.
+struct SmallJump {
+    bool first;
+    double be, cj;
+    double* jsum;
+    double* jback;
+};
+
+// One PI step (JUMP: one product of a jump) of a small level, rows shared by
+// `nthr` threads in G-lane groups.  Pointers are either all LDS (staged
+// modes) or all global.
+template <int G, bool W32, bool C16, bool LDS, bool JUMP>
 __device__ __forceinline__ void pi_small(int n, int nthr, const int32_t* rp, const void* colp,
                                          const void* wp, double g, const double* win, double* wout,
-                                         double mu, double s, double (&acc)[4]) {
+                                         double mu, double s, const SmallJump& sj, double (&acc)[4]) {
     const int lane = threadIdx.x & (G - 1);
     const int ngroups = nthr / G;
     for (int i = (int)(threadIdx.x / G); i < n; i += ngroups) {
         const int a = ldx<LDS>(rp, i), b = ldx<LDS>(rp, i + 1);
         const double wi = ldx<LDS>(win, i);
+        double sum = wi, z = 0.0;
+        if constexpr (JUMP) {
+            if (!sj.first && lane == 0) {
+                sum = gld(sj.jsum, i);
+                z = ldx<LDS>(wout, i);
+            }
+        }
         double t = 0.0;
         int e = a + lane;
         // four entries per trip: their column and value loads, then their
@@ -559,15 +576,109 @@ __device__ __forceinline__ void pi_small(int n, int nthr, const int32_t* rp, con
         }
         t = group_sum_t<G>(t);
         if (lane == 0) {
-            const double x = (wi - mu) * s;
-            const double y = s * (g * (wi - mu) + t);
-            stx<LDS>(wout, i, y);
-            acc[0] += y;
-            acc[1] += y * y;
-            acc[2] += y * x;
-            acc[3] += x;
+            if constexpr (JUMP) {
+                const double y = (sj.first ? wi : 2.0 * wi) + sj.be * t - z;
+                stx<LDS>(wout, i, y);
+                gst(sj.jsum, i, sum + sj.cj * y);
+                if (sj.first) gst(sj.jback, i, wi);
+                acc[0] += wi * y;
+                acc[1] += y * y;
+                acc[2] += wi * wi;
+            } else {
+                const double x = (wi - mu) * s;
+                const double y = s * (g * (wi - mu) + t);
+                stx<LDS>(wout, i, y);
+                acc[0] += y;
+                acc[1] += y * y;
+                acc[2] += y * x;
+                acc[3] += x;
+            }
         }
     }
+}
+
+// the same for a run-time G
+template <bool W32, bool C16, bool LDS, bool JUMP>
+__device__ __forceinline__ void pi_small_any(int G, int n, int nthr, const int32_t* rp, const void* colp,
+                                             const void* wp, double g, const double* win, double* wout, double mu,
+                                             double s, const SmallJump& sj, double (&acc)[4]) {
+    switch (G) {
+        case 1: pi_small<1, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        case 2: pi_small<2, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        case 4: pi_small<4, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        case 8: pi_small<8, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        case 16: pi_small<16, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        case 32: pi_small<32, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        default: pi_small<64, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+    }
+}
+
+// Moments and samples of a jump, and its verdict.
+struct JumpLds {
+    double mom[kJumpMoments];
+    double dl[kJumpSamples];
+    int safe, next;
+};
+
+// After each barrier of the waves that run the steps: count it and tell the
+// idle waves that more follow.
+template <bool WAVE>
+__device__ __forceinline__ void small_bar(int* stop_flag, int& bar) {
+    ++bar;
+    if (!WAVE && threadIdx.x == 0) stop_flag[bar & 1] = 0;
+}
+
+template <bool WAVE>
+__device__ __forceinline__ void small_sync(double* red, int& parity, int* stop_flag, int& bar, int nw) {
+    double z[4] = {0.0, 0.0, 0.0, 0.0};
+    step_sum4<WAVE>(z, red, parity, nw);
+    small_bar<WAVE>(stop_flag, bar);
+}
+
+// Mean and norm of b0, each entry written by the thread that reads it here.
+template <bool WAVE, bool LDS>
+__device__ __forceinline__ void small_normalise(int n, int nact, const double* b0, double* red, int& parity,
+                                                int* stop_flag, int& bar, int nw, double& mu, double& s) {
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i = threadIdx.x; i < n; i += nact) v[0] += ldx<LDS>(b0, i);
+    step_sum4<WAVE>(v, red, parity, nw);
+    small_bar<WAVE>(stop_flag, bar);
+    mu = v[0] / (double)n;
+    v[0] = v[1] = v[2] = v[3] = 0.0;
+    for (int i = threadIdx.x; i < n; i += nact) {
+        const double d = ldx<LDS>(b0, i) - mu;
+        v[0] += d * d;
+    }
+    step_sum4<WAVE>(v, red, parity, nw);
+    small_bar<WAVE>(stop_flag, bar);
+    s = 1.0 / sqrt(v[0]);
+}
+
+// Verdict on a jump whose products are done, the same in every running
+// thread; the moments are in js.
+template <bool WAVE>
+__device__ __forceinline__ bool small_jump_end(int K, int d, double tol, JumpLds* js, double* red, int& parity,
+                                               int* stop_flag, int& bar, int nw, int* more, int* hold) {
+    if (tol < 0.0) {
+        small_sync<WAVE>(red, parity, stop_flag, bar, nw);
+        return jump_verdict(K, 0, 0, true, more, hold);
+    }
+    small_sync<WAVE>(red, parity, stop_flag, bar, nw);
+    // a sample per running thread (at least 128, at most kJumpSamples)
+    const int ns = min(kJumpSamples, max(64 * nw, 128));
+    for (int q = threadIdx.x; q < ns; q += 64 * nw)
+        js->dl[q] = jump_delta(js->mom, 2 * d + 1, jump_sample(q, ns, K));
+    small_sync<WAVE>(red, parity, stop_flag, bar, nw);
+    if (threadIdx.x < 64) {
+        int safe, next;
+        jump_judge(js->dl, ns, K, tol, &safe, &next);
+        if (threadIdx.x == 0) {
+            js->safe = safe;
+            js->next = next;
+        }
+    }
+    small_sync<WAVE>(red, parity, stop_flag, bar, nw);
+    return jump_verdict(K, js->safe, js->next, false, more, hold);
 }
 
 struct SmallIn {
@@ -660,36 +771,43 @@ struct RegRows {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 
+    // sum over row r's entries a (w_k - w_i), in every lane of the group
+    __device__ __forceinline__ double row_sum(int r, const double* win, double wi) {
+        const int lane = (int)threadIdx.x & (G - 1);
+        const int i = row[r];
+        if constexpr (R * E > 32) {
+            // decode the columns and widen the weights every step:
+            // hoisted out of the step loop they would not fit
+#pragma unroll
+            for (int q = 0; q < E / 2; ++q) asm volatile("" : "+v"(c2[r][q]));
+#pragma unroll
+            for (int q = 0; q < E; ++q) asm volatile("" : "+v"(w[r][q]));
+        }
+        double x[E];
+#pragma unroll
+        for (int m = 0; m < E; ++m) x[m] = sld(win, (int)((m & 1) ? (c2[r][m >> 1] >> 16) : (c2[r][m >> 1] & 0xffffu)));
+        double t = 0.0;
+#pragma unroll
+        for (int m = 0; m < E; ++m) t += (double)w[r][m] * (x[m] - wi);
+        // entries beyond G E, two per trip; the second of a trip past
+        // the row's end is its own vertex with weight 0 (an exact zero)
+        for (int q = lane; q < ocnt[r]; q += 2 * G) {
+            const uint64_t p0 = sld(ovl, ooff[r] + q);
+            const uint64_t p1 = q + G < ocnt[r] ? sld(ovl, ooff[r] + q + G) : (uint64_t)(uint32_t)i;
+            const double x0 = sld(win, (int)(uint32_t)p0), x1 = sld(win, (int)(uint32_t)p1);
+            t += (double)__uint_as_float((uint32_t)(p0 >> 32)) * (x0 - wi);
+            t += (double)__uint_as_float((uint32_t)(p1 >> 32)) * (x1 - wi);
+        }
+        return group_sum_t<G>(t);
+    }
+
     __device__ __forceinline__ void step(const double* win, double* wout, double mu, double s, double (&acc)[4]) {
         const int lane = (int)threadIdx.x & (G - 1);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int i = row[r];
             const double wi = sld(win, i < 0 ? 0 : i);
-            if constexpr (R * E > 32) {
-                // decode the columns and widen the weights every step:
-                // hoisted out of the step loop they would not fit
-#pragma unroll
-                for (int q = 0; q < E / 2; ++q) asm volatile("" : "+v"(c2[r][q]));
-#pragma unroll
-                for (int q = 0; q < E; ++q) asm volatile("" : "+v"(w[r][q]));
-            }
-            double x[E];
-#pragma unroll
-            for (int m = 0; m < E; ++m) x[m] = sld(win, (int)((m & 1) ? (c2[r][m >> 1] >> 16) : (c2[r][m >> 1] & 0xffffu)));
-            double t = 0.0;
-#pragma unroll
-            for (int m = 0; m < E; ++m) t += (double)w[r][m] * (x[m] - wi);
-            // entries beyond G E, two per trip; the second of a trip past
-            // the row's end is its own vertex with weight 0 (an exact zero)
-            for (int q = lane; q < ocnt[r]; q += 2 * G) {
-                const uint64_t p0 = sld(ovl, ooff[r] + q);
-                const uint64_t p1 = q + G < ocnt[r] ? sld(ovl, ooff[r] + q + G) : (uint64_t)(uint32_t)i;
-                const double x0 = sld(win, (int)(uint32_t)p0), x1 = sld(win, (int)(uint32_t)p1);
-                t += (double)__uint_as_float((uint32_t)(p0 >> 32)) * (x0 - wi);
-                t += (double)__uint_as_float((uint32_t)(p1 >> 32)) * (x1 - wi);
-            }
-            t = group_sum_t<G>(t);
+            const double t = row_sum(r, win, wi);
             if (lane == 0 && i >= 0) {
                 const double xv = (wi - mu) * s;
                 const double y = s * (g * (wi - mu) + t);
@@ -701,6 +819,29 @@ struct RegRows {
             }
         }
     }
+
+    // one product of a jump, as in JumpOp, with the jump's sum and the
+    // vector before it in registers
+    __device__ __forceinline__ void product(const double* win, double* wout, bool first, double be, double cj,
+                                            double (&jsum)[R], double (&jback)[R], double (&acc)[4]) {
+        const int lane = (int)threadIdx.x & (G - 1);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = row[r];
+            const double wi = sld(win, i < 0 ? 0 : i);
+            const double z = sld(wout, i < 0 ? 0 : i);
+            const double t = row_sum(r, win, wi);
+            const double y = (first ? wi : 2.0 * wi - z) + be * t;
+            if (first) jback[r] = jsum[r] = wi;
+            jsum[r] += cj * y;
+            if (lane == 0 && i >= 0) {
+                sst(wout, i, y);
+                acc[0] += wi * y;
+                acc[1] += y * y;
+                acc[2] += wi * wi;
+            }
+        }
+    }
 };
 
 // Prolongation, deflation, normalisation and PI steps of one small level
@@ -708,7 +849,7 @@ struct RegRows {
 // image, whole workgroup; 2: global memory, whole workgroup.
 template <int MODE, bool W32, bool C16>
 __device__ void small_level(const LevelDev& L, const SmallIn& in, double* lds, double* red, int& parity,
-                            int* stop_flag, int nw_run, LevelState& out) {
+                            int* stop_flag, JumpLds* js, int nw_run, LevelState& out) {
     constexpr bool WAVE = (MODE == 0);
     constexpr bool LDS = (MODE != 2);
     const int n = L.n;
@@ -761,28 +902,25 @@ __device__ void small_level(const LevelDev& L, const SmallIn& in, double* lds, d
     int cur = 0, k = 0, hit = 0;
     double utv = 0.0, pmu = mu, ps = s;
     // The PI steps run on the first `nw` wavefronts; the others only keep
-    // the barrier count: after each barrier they read the stop decision of
-    // the step before it, and the running waves end with one more barrier.
+    // the barrier count: after each barrier they read the flag left after
+    // the one before it, and the running waves end with one more barrier.
     const int nw = WAVE ? 1 : nw_run;
     const int nact = 64 * nw;
     // wave-uniform test, taken as a scalar branch
     if (WAVE || __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < nw) {
+        const bool jumps = L.jmom != nullptr && (in.tol < 0.0 || in.tol >= kJumpTolMin);
+        int bar = 0;              // barriers passed
+        int since = 0, hold = 0;  // plain steps since the last jump, and to take before the next estimate
         while (true) {
             const double* win = cur ? b1 : b0;
             double* wout = cur ? b0 : b1;
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            switch (L.lanes) {
-                case 1: pi_small<1, W32, C16, LDS>(n, nact, rp, colp, wp, L.g, win, wout, mu, s, acc); break;
-                case 2: pi_small<2, W32, C16, LDS>(n, nact, rp, colp, wp, L.g, win, wout, mu, s, acc); break;
-                case 4: pi_small<4, W32, C16, LDS>(n, nact, rp, colp, wp, L.g, win, wout, mu, s, acc); break;
-                case 8: pi_small<8, W32, C16, LDS>(n, nact, rp, colp, wp, L.g, win, wout, mu, s, acc); break;
-                case 16: pi_small<16, W32, C16, LDS>(n, nact, rp, colp, wp, L.g, win, wout, mu, s, acc); break;
-                case 32: pi_small<32, W32, C16, LDS>(n, nact, rp, colp, wp, L.g, win, wout, mu, s, acc); break;
-                default: pi_small<64, W32, C16, LDS>(n, nact, rp, colp, wp, L.g, win, wout, mu, s, acc); break;
-            }
+            pi_small_any<W32, C16, LDS, false>(L.lanes, n, nact, rp, colp, wp, L.g, win, wout, mu, s, SmallJump{}, acc);
             step_sum4<WAVE>(acc, red, parity, nw);
+            ++bar;
             const double mu2 = acc[0] / (double)n;
             const double s2 = 1.0 / sqrt(acc[1] - acc[0] * mu2);
+            const double utvp = utv;
             utv = s2 * (acc[2] - mu2 * acc[3]);
             ++k;
             cur ^= 1;
@@ -795,13 +933,53 @@ __device__ void small_level(const LevelDev& L, const SmallIn& in, double* lds, d
                 hit = 1;
                 stop = true;
             }
-            if (!WAVE && threadIdx.x == 0) stop_flag[k & 1] = stop ? 1 : 0;
+            if (!WAVE && threadIdx.x == 0) stop_flag[bar & 1] = stop ? 1 : 0;
             if (stop) break;
+            if (hold > 0) {
+                --hold;
+                continue;
+            }
+            if (!jumps || !jump_due(++since)) continue;
+            const double r = 1.0 / (s * L.g);
+            int K = jump_plan(utv, utvp, in.tol, r, in.maxit - k - 1);
+            while (K > 0) {
+                const int d = jump_products(K);
+                SmallJump sj;
+                sj.jsum = L.jsum;
+                sj.jback = L.jback;
+                sj.cj = 2.0 * (double)K / (double)(K + 1);
+                for (int j = 0; j < d; ++j) {
+                    sj.first = j == 0;
+                    sj.be = (j == 0 ? 2.0 : 4.0) / L.g;
+                    double sum4[4] = {0.0, 0.0, 0.0, 0.0};
+                    pi_small_any<W32, C16, LDS, true>(L.lanes, n, nact, rp, colp, wp, L.g, cur ? b1 : b0,
+                                                      cur ? b0 : b1, mu, s, sj, sum4);
+                    step_sum4<WAVE>(sum4, red, parity, nw);
+                    small_bar<WAVE>(stop_flag, bar);
+                    if (threadIdx.x == 0) jump_moments(js->mom, j, sum4[0], sum4[1], sum4[2]);
+                    sj.cj = jump_coef(sj.cj, K, j + 1);
+                    cur ^= 1;
+                }
+                int more = 0;
+                const bool keep = small_jump_end<WAVE>(K, d, in.tol, js, red, parity, stop_flag, bar, nw, &more, &hold);
+                const double* src = keep ? L.jsum : L.jback;
+                for (int i = threadIdx.x; i < n; i += nact) stx<LDS>(b0, i, gld(src, i));
+                if (keep) {
+                    k += K;
+                    small_normalise<WAVE, LDS>(n, nact, b0, red, parity, stop_flag, bar, nw, mu, s);
+                } else {
+                    small_sync<WAVE>(red, parity, stop_flag, bar, nw);
+                }
+                cur = 0;
+                since = 0;
+                K = more > 0 ? jump_steps((double)more, r, in.maxit - k - 1) : 0;
+            }
         }
         if constexpr (!WAVE) __syncthreads();
     } else {
-        // barrier q closes step q unless step q - 1 was the last one; the
-        // slot parity follows the steps, as in the running waves
+        // the flag left after barrier q - 1 tells whether barrier q is the
+        // closing one; the slot parity follows the barriers, as in the
+        // running waves
         for (int q = 1;; ++q) {
             __syncthreads();
             if (q > 1 && stop_flag[(q - 1) & 1]) break;
@@ -852,6 +1030,7 @@ __global__ void __launch_bounds__(kBlockKernelThreads)
     __shared__ double s_cm, s_cs;
     __shared__ int s_cfin;
     __shared__ int s_stop[2];
+    __shared__ JumpLds s_jump;
     const BlockJob Jb = jobs[blockIdx.x];
     const LevelDev* __restrict__ lv = Jb.lv;
     int parity = 0;
@@ -914,23 +1093,23 @@ __global__ void __launch_bounds__(kBlockKernelThreads)
         if (mode == 0) {
             if (threadIdx.x < 64) {
                 if (w32) {
-                    if (c16) small_level<0, true, true>(L, in, lds, red, parity, s_stop, 1, o);
-                    else small_level<0, true, false>(L, in, lds, red, parity, s_stop, 1, o);
+                    if (c16) small_level<0, true, true>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
+                    else small_level<0, true, false>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
                 } else {
-                    if (c16) small_level<0, false, true>(L, in, lds, red, parity, s_stop, 1, o);
-                    else small_level<0, false, false>(L, in, lds, red, parity, s_stop, 1, o);
+                    if (c16) small_level<0, false, true>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
+                    else small_level<0, false, false>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
                 }
             }
         } else if (mode == 1) {
             if (w32) {
-                if (c16) small_level<1, true, true>(L, in, lds, red, parity, s_stop, nw, o);
-                else small_level<1, true, false>(L, in, lds, red, parity, s_stop, nw, o);
+                if (c16) small_level<1, true, true>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
+                else small_level<1, true, false>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
             } else {
-                if (c16) small_level<1, false, true>(L, in, lds, red, parity, s_stop, nw, o);
-                else small_level<1, false, false>(L, in, lds, red, parity, s_stop, nw, o);
+                if (c16) small_level<1, false, true>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
+                else small_level<1, false, false>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
             }
         } else {
-            small_level<2, false, false>(L, in, lds, red, parity, s_stop, nw, o);
+            small_level<2, false, false>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
         }
         if (threadIdx.x == 0) {
             o.ticks = wall_clock64() - t_start;
@@ -950,7 +1129,8 @@ __global__ void __launch_bounds__(kBlockKernelThreads)
 // steps and the others keep the barrier count as in the CSR traversal.
 template <int G, int R, int E>
 __device__ void reg_level(const LevelDev& L, const SmallIn& in, double* b0, double* b1, uint64_t* ov, int ovcap,
-                          int* ofill, double* red, int& parity, int* stop_flag, int* bad, int nw, LevelState& out) {
+                          int* ofill, double* red, int& parity, int* stop_flag, JumpLds* js, int* bad, int nw,
+                          LevelState& out) {
     const bool wave = (nw == 1);
     const int n = L.n;
     const int nthr = wave ? 64 : (int)blockDim.x;
@@ -983,7 +1163,7 @@ __device__ void reg_level(const LevelDev& L, const SmallIn& in, double* b0, doub
     double utv = 0.0, pmu = mu, ps = s;
     const int nact = 64 * nw;
     if (!(wave || __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < nw)) {
-        // barrier q closes step q unless step q - 1 was the last one
+        // counts the barriers along, as in the CSR traversal
         for (int q = 1;; ++q) {
             __syncthreads();
             if (q > 1 && stop_flag[(q - 1) & 1]) break;
@@ -993,6 +1173,9 @@ __device__ void reg_level(const LevelDev& L, const SmallIn& in, double* b0, doub
     }
     RegRows<G, R, E> rows;
     rows.load(L, nact, bad, ov, ovcap, ofill);
+    const bool jumps = L.jmom != nullptr && (in.tol < 0.0 || in.tol >= kJumpTolMin);
+    int bar = 0;              // barriers passed
+    int since = 0, hold = 0;  // plain steps since the last jump, and to take before the next estimate
     while (true) {
         const double* win = cur ? b1 : b0;
         double* wout = cur ? b0 : b1;
@@ -1000,8 +1183,10 @@ __device__ void reg_level(const LevelDev& L, const SmallIn& in, double* b0, doub
         rows.step(win, wout, mu, s, acc);
         if (wave) step_sum4<true>(acc, red, parity, 1);
         else step_sum4<false>(acc, red, parity, nw);
+        ++bar;
         const double mu2 = acc[0] / (double)n;
         const double s2 = 1.0 / sqrt(acc[1] - acc[0] * mu2);
+        const double utvp = utv;
         utv = s2 * (acc[2] - mu2 * acc[3]);
         ++k;
         cur ^= 1;
@@ -1014,8 +1199,48 @@ __device__ void reg_level(const LevelDev& L, const SmallIn& in, double* b0, doub
             hit = 1;
             stop = true;
         }
-        if (!wave && threadIdx.x == 0) stop_flag[k & 1] = stop ? 1 : 0;
+        if (!wave && threadIdx.x == 0) stop_flag[bar & 1] = stop ? 1 : 0;
         if (stop) break;
+        if (hold > 0) {
+            --hold;
+            continue;
+        }
+        if (!jumps || !jump_due(++since)) continue;
+        const double r = 1.0 / (s * L.g);
+        int K = jump_plan(utv, utvp, in.tol, r, in.maxit - k - 1);
+        while (K > 0) {
+            const int d = jump_products(K);
+            double cj = 2.0 * (double)K / (double)(K + 1);
+            double jsum[R], jback[R];
+            for (int j = 0; j < d; ++j) {
+                double sum4[4] = {0.0, 0.0, 0.0, 0.0};
+                rows.product(cur ? b1 : b0, cur ? b0 : b1, j == 0, (j == 0 ? 2.0 : 4.0) / L.g, cj, jsum, jback, sum4);
+                if (wave) step_sum4<true>(sum4, red, parity, 1);
+                else step_sum4<false>(sum4, red, parity, nw);
+                if (wave) small_bar<true>(stop_flag, bar);
+                else small_bar<false>(stop_flag, bar);
+                if (threadIdx.x == 0) jump_moments(js->mom, j, sum4[0], sum4[1], sum4[2]);
+                cj = jump_coef(cj, K, j + 1);
+                cur ^= 1;
+            }
+            int more = 0;
+            const bool keep =
+                wave ? small_jump_end<true>(K, d, in.tol, js, red, parity, stop_flag, bar, 1, &more, &hold)
+                     : small_jump_end<false>(K, d, in.tol, js, red, parity, stop_flag, bar, nw, &more, &hold);
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+                if (((int)threadIdx.x & (G - 1)) == 0 && rows.row[q] >= 0) sst(b0, rows.row[q], keep ? jsum[q] : jback[q]);
+            if (wave) small_sync<true>(red, parity, stop_flag, bar, 1);
+            else small_sync<false>(red, parity, stop_flag, bar, nw);
+            if (keep) {
+                k += K;
+                if (wave) small_normalise<true, true>(n, 64, b0, red, parity, stop_flag, bar, 1, mu, s);
+                else small_normalise<false, true>(n, nact, b0, red, parity, stop_flag, bar, nw, mu, s);
+            }
+            cur = 0;
+            since = 0;
+            K = more > 0 ? jump_steps((double)more, r, in.maxit - k - 1) : 0;
+        }
     }
     if (!wave) __syncthreads();
     // the LDS vectors are discarded: final vector to buf0, previous to buf1
@@ -1056,6 +1281,7 @@ __global__ void __launch_bounds__(kBlockRegsThreads)
     __shared__ double s_cm, s_cs;
     __shared__ int s_cfin;
     __shared__ int s_stop[2];
+    __shared__ JumpLds s_jump;
     __shared__ int s_bad;
     __shared__ int s_ofill;
     const BlockJob Jb = jobs[blockIdx.x];
@@ -1103,9 +1329,9 @@ __global__ void __launch_bounds__(kBlockRegsThreads)
             o.err = 2;
         } else if (nw == 1) {
             if (threadIdx.x < 64)
-                reg_level<G, R, E>(L, in, lds, lds + n, ov, ovcap, &s_ofill, red, parity, s_stop, &s_bad, 1, o);
+                reg_level<G, R, E>(L, in, lds, lds + n, ov, ovcap, &s_ofill, red, parity, s_stop, &s_jump, &s_bad, 1, o);
         } else {
-            reg_level<G, R, E>(L, in, lds, lds + n, ov, ovcap, &s_ofill, red, parity, s_stop, &s_bad, nw, o);
+            reg_level<G, R, E>(L, in, lds, lds + n, ov, ovcap, &s_ofill, red, parity, s_stop, &s_jump, &s_bad, nw, o);
         }
         if (threadIdx.x == 0) {
             o.ticks = wall_clock64() - t_start;
@@ -1237,6 +1463,52 @@ struct PiOp {
         acc[1] += yd * yd;
         acc[2] += yd * v;
         acc[3] += v;
+    }
+};
+
+// One product of a jump (jump.h): y_i = al x_i + be (-L x)_i - ga z_i with z
+// the vector before x, which y replaces (the first product has ga = 0 and
+// keeps x in jback); jsum += cj y; acc = {(x, y), (y, y), (x, x)}.
+template <int WK, bool STG = false>
+struct JumpOp {
+    const int32_t* __restrict__ col;
+    WRead<typename WStore<double, WK>::type, STG> wv;
+    const double* __restrict__ win;
+    double* wout;
+    double* jsum;
+    double* jback;
+    int roff;
+    bool first;
+    double be, cj;
+    double acc[3];
+    __device__ __forceinline__ double xi(int i) const { return gld(win, roff + i); }
+    __device__ __forceinline__ int vidx(int i) const { return roff + i; }
+    __device__ __forceinline__ int colof(int e) const {
+        if constexpr (STG) return sld(col, e);
+        else return gld(col, e);
+    }
+    __device__ __forceinline__ double wof(int e) const { return wv[e]; }
+    __device__ __forceinline__ double xk(int c) const { return gld(win, c); }
+    __device__ __forceinline__ double term(double xc, double wt, double x) const { return wt * (xc - x); }
+    __device__ __forceinline__ double entry(int e, double x) const { return term(xk(colof(e)), wof(e), x); }
+    __device__ __forceinline__ double entry_cw(int c, double wt, double x) const { return term(xk(c), wt, x); }
+    __device__ __forceinline__ void row(int i, double x, double t) {
+        const int q = roff + i;
+        double y, sum;
+        if (first) {
+            y = x + be * t;
+            sum = x;
+            gst(jback, q, x);
+        } else {
+            const double z = gld(wout, q);
+            sum = gld(jsum, q);
+            y = 2.0 * x + be * t - z;
+        }
+        gst(wout, q, y);
+        gst(jsum, q, sum + cj * y);
+        acc[0] += x * y;
+        acc[1] += y * y;
+        acc[2] += x * x;
     }
 };
 
@@ -1677,6 +1949,92 @@ struct StageLds {
     double w[kStageEnts];
 };
 
+// ---- the products of a jump over K steps (jump.h) from buf[cur], whose sum
+// is left in jsum, and the verdict's inputs: the first workgroup keeps the
+// moments, samples (u, v) over the jump and sends the result to the others.
+// Rows are shared as in the plain steps (see refine_level).
+template <int TRAV, int WK>
+__device__ __forceinline__ bool jump_products_run(const LevelDev& L, GridCtx& c, int K, double tol, int cur,
+                                                  bool staged, StageLds* stg, MergeShared* sh, double* red, int r0,
+                                                  int r1, int x0, int x1, int xp, int np, int& safe, int& next) {
+    using WT = typename WStore<double, WK>::type;
+    const int d = jump_products(K);
+    double cj = 2.0 * (double)K / (double)(K + 1);
+    double* bufs[2] = {(double*)L.buf0, (double*)L.buf1};
+    const double be1 = 2.0 / L.g;
+    for (int j = 0; j < d; ++j) {
+        double acc[3];
+        if (TRAV > 0 && staged) {
+            if constexpr (TRAV > 0) {
+                JumpOp<WK, true> op;
+                op.col = stg->col;
+                if constexpr (WK != kWUnit) op.wv.p = (const WT*)stg->w;
+                op.win = cur ? bufs[1] : bufs[0];
+                op.wout = cur ? bufs[0] : bufs[1];
+                op.jsum = L.jsum;
+                op.jback = L.jback;
+                op.roff = r0;
+                op.first = j == 0;
+                op.be = j == 0 ? be1 : 2.0 * be1;
+                op.cj = cj;
+                op.acc[0] = op.acc[1] = op.acc[2] = 0.0;
+                drive_rows<TRAV, true>(stg->rp, 0, r1 - r0, op, L.lrows, L.lmin, red, r0);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) acc[q] = op.acc[q];
+            }
+        } else {
+            JumpOp<WK> op;
+            op.col = L.col;
+            op.wv = weights_of<double, WK>(L);
+            op.win = cur ? bufs[1] : bufs[0];
+            op.wout = cur ? bufs[0] : bufs[1];
+            op.jsum = L.jsum;
+            op.jback = L.jback;
+            op.roff = 0;
+            op.first = j == 0;
+            op.be = j == 0 ? be1 : 2.0 * be1;
+            op.cj = cj;
+            op.acc[0] = op.acc[1] = op.acc[2] = 0.0;
+            if constexpr (TRAV == 0) {
+                drive_merge(L.rp, r0, r1, op, *sh);
+            } else if (L.ileave) {
+                const int cw = 4 * ((int)blockDim.x / TRAV);
+                for (int a = x0 + xp * cw; a < x1; a += np * cw)
+                    drive_rows<TRAV>(L.rp, a, min(a + cw, x1), op, nullptr, L.lmin, red);
+                if (L.lrows != nullptr) drive_long_rows<false, (TRAV >= 32)>(L.rp, r0, r1, op, L.lrows, red);
+            } else {
+                drive_rows<TRAV>(L.rp, r0, r1, op, L.lrows, L.lmin, red);
+            }
+#pragma unroll
+            for (int q = 0; q < 3; ++q) acc[q] = op.acc[q];
+        }
+        if (!job_allreduce<3>(acc, c, red)) return false;
+        if (c.vb == 0 && threadIdx.x == 0) jump_moments(L.jmom, j, acc[0], acc[1], acc[2]);
+        cj = jump_coef(cj, K, j + 1);
+        cur ^= 1;
+    }
+    double vd[2] = {0.0, 0.0};
+    if (c.vb == 0 && tol >= 0.0) {
+        double* dl = L.jmom + kJumpMoments;
+        __syncthreads();
+        for (int q = threadIdx.x; q < kJumpSamples; q += blockDim.x)
+            dl[q] = jump_delta(L.jmom, 2 * d + 1, jump_sample(q, kJumpSamples, K));
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            int sf, nx;
+            jump_judge(dl, kJumpSamples, K, tol, &sf, &nx);
+            if (threadIdx.x == 0) {
+                vd[0] = (double)sf;
+                vd[1] = (double)nx;
+            }
+        }
+    }
+    if (!job_allreduce<2>(vd, c, red)) return false;
+    safe = (int)vd[0];
+    next = (int)vd[1];
+    return true;
+}
+
 // ---- refinement of one level by a job's workgroups
 
 template <typename T, int TRAV, int WK>
@@ -1745,17 +2103,25 @@ __device__ void refine_level(const GridJob& J, GridCtx& c, double* red, MergeSha
             sum[0] += (double)v;
         }
     }
-    if (!job_allreduce<1>(sum, c, red)) return;
-    double mu = sum[0] / n;
-    double ss[1] = {0.0};
-    for (int i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
-        const double d = (double)gld(b0, i) - mu;
-        ss[0] += d * d;
-    }
-    if (!job_allreduce<1>(ss, c, red)) return;
-    double s = 1.0 / sqrt(ss[0]);
+    // mean and norm of the vector in b0, whose sum the workgroups hold
+    double mu = 0.0, s = 0.0;
+    auto normalise = [&](double (&sm)[1]) -> bool {
+        if (!job_allreduce<1>(sm, c, red)) return false;
+        mu = sm[0] / n;
+        double ss[1] = {0.0};
+        for (int i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
+            const double d = (double)gld(b0, i) - mu;
+            ss[0] += d * d;
+        }
+        if (!job_allreduce<1>(ss, c, red)) return false;
+        s = 1.0 / sqrt(ss[0]);
+        return true;
+    };
+    if (!normalise(sum)) return;
     int cur = 0, k = 0, hit = 0;
     double utv = 0.0, pmu = mu, ps = s;
+    const bool jumps = sizeof(T) == 8 && L.jmom != nullptr && (tol < 0.0 || tol >= kJumpTolMin);
+    int since = 0, hold = 0;  // plain steps since the last jump, and to take before the next estimate
     while (true) {
         double acc[4];
         if (TRAV > 0 && staged) {
@@ -1790,6 +2156,7 @@ __device__ void refine_level(const GridJob& J, GridCtx& c, double* red, MergeSha
         if (!job_allreduce<4>(acc, c, red)) return;
         const double mu2 = acc[0] / n;
         const double s2 = 1.0 / sqrt(acc[1] - acc[0] * mu2);
+        const double utvp = utv;
         utv = s2 * (acc[2] - mu2 * acc[3]);
         ++k;
         cur ^= 1;
@@ -1801,6 +2168,39 @@ __device__ void refine_level(const GridJob& J, GridCtx& c, double* red, MergeSha
         if (k >= maxit) {
             hit = 1;
             break;
+        }
+        if constexpr (sizeof(T) == 8) {
+            if (hold > 0) {
+                --hold;
+                continue;
+            }
+            if (!jumps || !jump_due(++since)) continue;
+            const double r = 1.0 / (s * L.g);
+            int K = jump_plan(utv, utvp, tol, r, maxit - k - 1);
+            while (K > 0) {
+                int safe = 0, next = 0;
+                if (!jump_products_run<TRAV, WK>(L, c, K, tol, cur, staged, stg, sh, red, r0, r1, x0, x1, xp, np, safe,
+                                                 next))
+                    return;
+                int more = 0;
+                double sm[1] = {0.0};
+                since = 0;
+                cur = 0;
+                if (jump_verdict(K, safe, next, tol < 0.0, &more, &hold)) {
+                    k += K;
+                    for (int i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
+                        const double v = gld(L.jsum, i);
+                        gst((double*)L.buf0, i, v);
+                        sm[0] += v;
+                    }
+                    if (!normalise(sm)) return;
+                } else {
+                    for (int i = r0 + threadIdx.x; i < r1; i += blockDim.x)
+                        gst((double*)L.buf0, i, gld(L.jback, i));
+                    if (!job_allreduce<1>(sm, c, red)) return;
+                }
+                K = more > 0 ? jump_steps((double)more, r, maxit - k - 1) : 0;
+            }
         }
     }
     if (c.vb == 0 && threadIdx.x == 0) {
@@ -2118,6 +2518,8 @@ __global__ void __launch_bounds__(kCheckThreads) k_step_norm(const StepJob* __re
         c->cur = 0;
         c->done = 0;
         c->hit = 0;
+        c->mode = 0;
+        c->since = c->hold = c->more = 0;
     }
 }
 
@@ -2131,6 +2533,37 @@ __global__ void __launch_bounds__(kStepBlock) k_step_spmv(const StepJob* __restr
     const LevelDev& L = J.L;
     const int lb = xcd_remap((int)blockIdx.x, (int)gridDim.x);  // row block, posted in row order
     const int r0 = L.part[lb], r1 = L.part[lb + 1];
+    if constexpr (sizeof(T) == 8) {
+        if (c.mode > 2) {  // the end of a jump (StepCtl)
+            double* b0 = (double*)L.buf0;
+            const double* src = c.mode == 3 ? L.jsum : c.mode == 4 ? b0 : L.jback;
+            double sum[3] = {0.0, 0.0, 0.0};
+            for (int i = r0 + threadIdx.x; i < r1; i += blockDim.x) {
+                const double v = gld(src, i);
+                if (c.mode != 4) gst(b0, i, v);
+                sum[0] += c.mode == 4 ? (v - c.mu) * (v - c.mu) : v;
+            }
+            post_part<3>(sum, red, J.part, lb);
+            return;
+        }
+        if (c.mode > 0) {  // a product of a jump
+            JumpOp<WK> op;
+            op.col = L.col;
+            op.wv = weights_of<double, WK>(L);
+            op.win = (const double*)(c.cur ? L.buf1 : L.buf0);
+            op.wout = (double*)(c.cur ? L.buf0 : L.buf1);
+            op.jsum = L.jsum;
+            op.jback = L.jback;
+            op.roff = 0;
+            op.first = c.mode == 1;
+            op.be = (c.mode == 1 ? 2.0 : 4.0) / L.g;
+            op.cj = c.cj;
+            op.acc[0] = op.acc[1] = op.acc[2] = 0.0;
+            drive_rows<G, false, (G >= 32)>(L.rp, r0, r1, op, L.lrows, L.lmin, red);
+            post_part<3>(op.acc, red, J.part, lb);
+            return;
+        }
+    }
     PiOp<T, WK> op;
     op.col = L.col;
     op.wv = weights_of<T, WK>(L);
@@ -2145,19 +2578,30 @@ __global__ void __launch_bounds__(kStepBlock) k_step_spmv(const StepJob* __restr
     post_part<4>(op.acc, red, J.part, lb);
 }
 
+// arms a jump of K steps (0: plain steps)
+__device__ __forceinline__ void step_arm(StepCtl& c, int K) {
+    c.mode = K > 0 ? 1 : 0;
+    c.j = 0;
+    c.K = K;
+    c.d = jump_products(K);
+    c.cj = 2.0 * (double)K / (double)(K + 1);
+}
+
 // sums of the step, stopping test, state for the next step; writes the
 // level state when the level is done
 __global__ void __launch_bounds__(kCheckThreads) k_step_check(const StepJob* __restrict__ jp, int nb) {
     __shared__ double red[16 * 5 + 8];
     const StepJob J = *jp;
-    if (J.ctl->done) return;
+    StepCtl c = *J.ctl;
+    if (c.done) return;
+    const double n = (double)J.L.n;
     double acc[4];
     sum_parts<4>(J.part, nb, acc, red);
-    if (threadIdx.x == 0) {
-        StepCtl c = *J.ctl;
-        const double n = (double)J.L.n;
+    if (c.mode == 0) {
+        if (threadIdx.x != 0) return;
         const double mu2 = acc[0] / n;
         const double s2 = 1.0 / sqrt(acc[1] - acc[0] * mu2);
+        c.utvp = c.utv;
         c.utv = s2 * (acc[2] - mu2 * acc[3]);
         ++c.k;
         c.cur ^= 1;
@@ -2170,6 +2614,11 @@ __global__ void __launch_bounds__(kCheckThreads) k_step_check(const StepJob* __r
         } else if (c.k >= J.maxit) {
             c.done = 1;
             c.hit = 1;
+        } else if (c.hold > 0) {
+            --c.hold;
+        } else if (J.L.jmom != nullptr && J.tol >= kJumpTolMin && jump_due(++c.since)) {
+            c.r = 1.0 / (c.s * J.L.g);
+            step_arm(c, jump_plan(c.utv, c.utvp, J.tol, c.r, J.maxit - c.k - 1));
         }
         *J.ctl = c;
         if (c.done) {
@@ -2187,7 +2636,38 @@ __global__ void __launch_bounds__(kCheckThreads) k_step_check(const StepJob* __r
             o.ticks = 0;
             *J.st = o;
         }
+        return;
     }
+    if (c.mode <= 2) {
+        double* mom = J.L.jmom;
+        if (threadIdx.x == 0) jump_moments(mom, c.j, acc[0], acc[1], acc[2]);
+        ++c.j;
+        c.cj = jump_coef(c.cj, c.K, c.j);
+        c.cur ^= 1;
+        c.mode = 2;
+        if (c.j == c.d) {  // the last product: sample (u, v) over the jump
+            double* dl = mom + kJumpMoments;
+            __syncthreads();
+            for (int q = threadIdx.x; q < kJumpSamples; q += blockDim.x)
+                dl[q] = jump_delta(mom, 2 * c.d + 1, jump_sample(q, kJumpSamples, c.K));
+            __syncthreads();
+            if (threadIdx.x >= 64) return;
+            int safe, next;
+            jump_judge(dl, kJumpSamples, c.K, J.tol, &safe, &next);
+            c.since = 0;
+            const bool keep = jump_verdict(c.K, safe, next, false, &c.more, &c.hold);
+            if (keep) c.k += c.K;
+            c.mode = keep ? 3 : 5;
+        }
+    } else if (c.mode == 3) {
+        c.mu = acc[0] / n;
+        c.mode = 4;
+    } else {
+        if (c.mode == 4) c.s = 1.0 / sqrt(acc[0]);
+        c.cur = 0;
+        step_arm(c, c.more > 0 ? jump_steps((double)c.more, c.r, J.maxit - c.k - 1) : 0);
+    }
+    if (threadIdx.x == 0) *J.ctl = c;
 }
 
 }  // namespace
