@@ -34,56 +34,79 @@ inline unsigned nblocks(int64_t m, int per) { return (unsigned)((m + per - 1) / 
 // One group of kValidateLanes lanes per row (row n: the row-pointer ends);
 // each lane checks every kValidateLanes-th entry of the row against the
 // entry before it.
+//
+// The findings are not only faults: graphs that are not all ones, or whose
+// weights are not all integers, raise a flag in every row.  Each workgroup
+// therefore gathers its rows' flags and longest row first and touches the
+// two global words at most once, and only with bits they lack (an atomic
+// per wavefront on one address had set the time: 1M vertices, 10M integer
+// weights 1427 us).
 constexpr int kValidateLanes = 8;
+constexpr unsigned kValidateBlocks = 2048;
 
 template <typename W>
-__global__ void k_validate(int n, int64_t nnz, const int32_t* __restrict__ rp,
-                           const int32_t* __restrict__ col, const W* __restrict__ w, int full,
-                           unsigned* flags) {
+__global__ void __launch_bounds__(kBlk) k_validate(int n, int64_t nnz, const int32_t* __restrict__ rp,
+                                                   const int32_t* __restrict__ col, const W* __restrict__ w, int full,
+                                                   unsigned* flags) {
+    __shared__ unsigned s_f, s_len;
+    if (threadIdx.x == 0) s_f = s_len = 0u;
+    __syncthreads();
     const int lane = threadIdx.x & (kValidateLanes - 1);
-    const int i = blockIdx.x * (blockDim.x / kValidateLanes) + threadIdx.x / kValidateLanes;
-    if (i > n) return;
-    unsigned f = 0;
-    if (i == n) {
-        if (lane == 0 && ((int64_t)rp[n] != nnz || rp[0] != 0)) f |= kBadGraph;
-    } else {
+    const int64_t ngroups = (int64_t)gridDim.x * (blockDim.x / kValidateLanes);
+    unsigned f = 0, len = 0;
+    for (int64_t q = (int64_t)blockIdx.x * (blockDim.x / kValidateLanes) + threadIdx.x / kValidateLanes; q <= n;
+         q += ngroups) {
+        const int i = (int)q;
+        if (i == n) {
+            if (lane == 0 && ((int64_t)rp[n] != nnz || rp[0] != 0)) f |= kBadGraph;
+            continue;
+        }
         const int a = rp[i], b = rp[i + 1];
         if (a < 0 || b < a || (int64_t)b > nnz) {
             f |= kBadGraph;
-        } else if (a == b) {
+            continue;
+        }
+        if (a == b) {
             f |= kIsolated;
-        } else {
-            if (lane == 0 && b - a > 64) atomicMax(&flags[1], (unsigned)(b - a));  // long rows only
-            for (int e = a + lane; e < b; e += kValidateLanes) {
-                const int c = col[e];
-                const int prev = e > a ? col[e - 1] : -1;
-                const double x = (double)w[e];
-                bool bad = c < 0 || c >= n || c == i || c <= prev;
-                if (!(x > 0.0) || !isfinite(x)) bad = true;
-                if (!bad && (x != floor(x) || x >= 1048576.0)) f |= kWideWeight;
-                if (x != 1.0) f |= kNonUnit;
-                if (bad) {
-                    f |= kBadGraph;
-                } else if (full && rp[c] >= 0 && rp[c] <= rp[c + 1] && (int64_t)rp[c + 1] <= nnz) {
-                    // binary search i in row c, weights must agree
-                    int lo = rp[c], hi = rp[c + 1] - 1;
-                    bool found = false;
-                    while (lo <= hi) {
-                        const int mid = (lo + hi) >> 1;
-                        const int cm = col[mid];
-                        if (cm == i) {
-                            found = ((double)w[mid] == x);
-                            break;
-                        }
-                        if (cm < i) lo = mid + 1;
-                        else hi = mid - 1;
+            continue;
+        }
+        if (b - a > 64) len = max(len, (unsigned)(b - a));  // long rows only
+        for (int e = a + lane; e < b; e += kValidateLanes) {
+            const int c = col[e];
+            const int prev = e > a ? col[e - 1] : -1;
+            const double x = (double)w[e];
+            bool bad = c < 0 || c >= n || c == i || c <= prev;
+            if (!(x > 0.0) || !isfinite(x)) bad = true;
+            if (!bad && (x != floor(x) || x >= 1048576.0)) f |= kWideWeight;
+            if (x != 1.0) f |= kNonUnit;
+            if (bad) {
+                f |= kBadGraph;
+            } else if (full && rp[c] >= 0 && rp[c] <= rp[c + 1] && (int64_t)rp[c + 1] <= nnz) {
+                // binary search i in row c, weights must agree
+                int lo = rp[c], hi = rp[c + 1] - 1;
+                bool found = false;
+                while (lo <= hi) {
+                    const int mid = (lo + hi) >> 1;
+                    const int cm = col[mid];
+                    if (cm == i) {
+                        found = ((double)w[mid] == x);
+                        break;
                     }
-                    if (!found) f |= kAsym;
+                    if (cm < i) lo = mid + 1;
+                    else hi = mid - 1;
                 }
+                if (!found) f |= kAsym;
             }
         }
     }
-    if (f) atomicOr(flags, f);
+    if (f) atomicOr(&s_f, f);
+    if (len) atomicMax(&s_len, len);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (s_f & ~__hip_atomic_load(&flags[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(&flags[0], s_f);
+        if (s_len > __hip_atomic_load(&flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(&flags[1], s_len);
+    }
 }
 
 template <typename W>
@@ -1218,7 +1241,7 @@ __global__ void k_fill_u32(unsigned* p, unsigned v, int64_t m) {
 
 hipError_t launch_validate(int n, int64_t nnz, const int32_t* rp, const int32_t* col, const void* w,
                            int wf32, int full, unsigned* flags, hipStream_t s) {
-    unsigned nb = nblocks((int64_t)n + 1, kBlk / kValidateLanes);
+    const unsigned nb = std::min(nblocks((int64_t)n + 1, kBlk / kValidateLanes), kValidateBlocks);
     if (wf32)
         hipLaunchKernelGGL(k_validate<float>, dim3(nb), dim3(kBlk), 0, s, n, nnz, rp, col,
                            (const float*)w, full, flags);
