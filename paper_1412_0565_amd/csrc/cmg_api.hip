@@ -1175,7 +1175,7 @@ cmg_status build_refine_plan(cmg_ctx* c) {
         LJ.buf0 = c->dalloc(sizeof(double) * (size_t)LJ.n);
         LJ.buf1 = c->dalloc(sizeof(double) * (size_t)LJ.n);
         if (!LJ.buf0 || !LJ.buf1) return CMG_E_OOM;
-        const int dm = std::max(CJ.n, 2);
+        const int dm = std::max(CJ.n, 2) + 1;  // an odd order is solved with one row and column more
         ALLOC(c->d_A, double, (size_t)dm * dm);
         ALLOC(c->d_V, double, (size_t)dm * dm);
         ALLOC(c->d_ev, double, 2 * (size_t)dm);

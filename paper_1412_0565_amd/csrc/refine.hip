@@ -216,142 +216,162 @@ __device__ __forceinline__ void pi_rows_dispatch(int G, const LevelDev& L, const
 // coarsest levels up to this size keep A and V in LDS (2 n^2 doubles)
 constexpr int kDenseLds = 48;
 
-// Dense coarsest solve in one workgroup: L^J assembled densely, Jacobi
-// eigenvalue iteration with the parallel round-robin ("tournament") order
-// (n/2 disjoint plane rotations per step, n-1 steps per sweep; disjoint
-// rotations commute, so a step equals applying them one after another),
-// until the off-diagonal norm is <= 1e-14 ||A||_F.  The vector is the
-// normalised projection of the ramp z_i = i - (n-1)/2 onto the eigenspace
-// of all eigenvalues (above the smallest) within 1e-10 ||A||_F of
-// lambda_2; a hashed uniform vector replaces z if that projection is tiny.
+// 1/x and 1/sqrt(x) to double rounding for normal x (hardware estimate and
+// two Newton steps: a quarter of the latency of a division or square root)
+__device__ __forceinline__ double fast_rcp(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(y, fma(-x, y, 1.0), y);
+    return fma(y, fma(-x, y, 1.0), y);
+}
+__device__ __forceinline__ double fast_rsq(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+
+// Sweeps of the Jacobi iteration in the parallel round-robin
+// ("tournament") order on the m x m matrix A (m even, row-major), rotations
+// collected in V: m/2 disjoint plane rotations per step, m - 1 steps per
+// sweep (disjoint rotations commute, so a step equals applying them one
+// after another), until the off-diagonal norm is <= 1e-14 fro.  A step is
+// two barriers: the pairs' rotations, then every 2 x 2 block of J^T A J (a
+// thread per pair of pairs) and every row of V J.  It is bound by the
+// latency of the rotation (estimates in place of two divisions and two
+// square roots) and of its LDS trips: n = 25 measured 372 us with rows,
+// columns and eigenvalue order in turn.
+__device__ __forceinline__ void jacobi_sweeps(double* A, double* V, int m, double fro, double* red, double* cs,
+                                              double* sn, int* pp, int* qq) {
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const int np = m / 2;
+    const float inv = 1.0f / (float)np;
+    for (int sweep = 0; sweep < 50; ++sweep) {
+        double o[1] = {0.0};
+        for (int t = tid; t < m * m; t += nt)
+            if (t / m != t % m) o[0] += A[t] * A[t];
+        block_sum<1>(o, red);
+        if (sqrt(o[0]) <= 1e-14 * fro) break;
+        for (int step = 0; step < m - 1; ++step) {
+            for (int i = tid; i < np; i += nt) {
+                int a = 0, b = step + 1;
+                if (i > 0) {
+                    a = step + i >= m - 1 ? step + i - (m - 1) + 1 : step + i + 1;
+                    b = step - i < 0 ? step - i + (m - 1) + 1 : step - i + 1;
+                }
+                const int p = min(a, b), q = max(a, b);
+                const double apq = A[p * m + q];
+                double c = 1.0, s = 0.0;
+                if (fabs(apq) > 1e-30 * fro) {
+                    const double tau = 0.5 * (A[q * m + q] - A[p * m + p]) * fast_rcp(apq);
+                    const double w = 1.0 + tau * tau;
+                    const double t = copysign(fast_rcp(fabs(tau) + w * fast_rsq(w)), tau);
+                    c = fast_rsq(1.0 + t * t);
+                    s = t * c;
+                }
+                pp[i] = p;
+                qq[i] = q;
+                cs[i] = c;
+                sn[i] = s;
+            }
+            __syncthreads();
+            for (int t = tid; t < np * np + np * m; t += nt) {
+                // t / np by a float product (t < 2^14, exact half-way off an integer)
+                const int tq = (int)(((float)t + 0.5f) * inv);
+                if (t < np * np) {  // rows of pair i, columns of pair j
+                    const int i = tq, j = t - i * np;
+                    const int ri = pp[i] * m, rq = qq[i] * m, cj = pp[j], cq = qq[j];
+                    const double ci = cs[i], si = sn[i], c = cs[j], s = sn[j];
+                    const double x = A[ri + cj], y = A[ri + cq], z = A[rq + cj], w = A[rq + cq];
+                    const double x1 = ci * x - si * z, y1 = ci * y - si * w;
+                    const double z1 = si * x + ci * z, w1 = si * y + ci * w;
+                    A[ri + cj] = c * x1 - s * y1;
+                    A[ri + cq] = s * x1 + c * y1;
+                    A[rq + cj] = c * z1 - s * w1;
+                    A[rq + cq] = s * z1 + c * w1;
+                } else {  // row k of V
+                    const int k = tq - np, j = t - tq * np;
+                    const int cj = k * m + pp[j], cq = k * m + qq[j];
+                    const double c = cs[j], s = sn[j];
+                    const double x = V[cj], y = V[cq];
+                    V[cj] = c * x - s * y;
+                    V[cq] = s * x + c * y;
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// Dense coarsest solve in one workgroup: L^J assembled densely (a zero row
+// and column make an odd order even), its eigenvectors by Jacobi iteration.
+// The vector is the normalised projection of the ramp z_i = i - (n-1)/2
+// onto the eigenspace of all eigenvalues (above the smallest) within
+// 1e-10 ||A||_F of lambda_2; a hashed uniform vector replaces z if that
+// projection is tiny.
 __global__ void __launch_bounds__(256) k_coarse_jobs(const CoarseJob* __restrict__ jobs) {
     extern __shared__ double dyn[];
     const CoarseJob& Jb = jobs[blockIdx.x];
     const LevelDev L = Jb.L;
     LevelState* st = Jb.st;
-    double* Ag = Jb.A;
     double* Vg = Jb.V;
-    double* ev = Jb.ev;
-    int32_t* idx = Jb.idx;
     const uint64_t seed = Jb.seed;
     FinishOut* fo = Jb.fo;
     __shared__ double red[16 * 2 + 8];
-    __shared__ double cs_c[128], cs_s[128];
-    __shared__ int pr_p[128], pr_q[128];
+    __shared__ double cs_c[64], cs_s[64], ev[128], dots[128];
+    __shared__ int pr_p[64], pr_q[64], idx[128];
     const int n = L.n;
+    const int m = n + (n & 1);
     const int tid = threadIdx.x, nt = blockDim.x;
-    double* A = (n <= kDenseLds) ? dyn : Ag;
-    double* V = (n <= kDenseLds) ? dyn + n * n : Vg;
-    for (int t = tid; t < n * n; t += nt) {
+    const bool lds = n <= kDenseLds;
+    double* A = lds ? dyn : Jb.A;
+    double* V = lds ? dyn + m * m : Vg;
+    for (int t = tid; t < m * m; t += nt) {
         A[t] = 0.0;
-        V[t] = ((t / n) == (t % n)) ? 1.0 : 0.0;
+        V[t] = ((t / m) == (t % m)) ? 1.0 : 0.0;
     }
     __syncthreads();
     for (int i = tid; i < n; i += nt) {
         double d = 0.0;
         for (int e = L.rp[i]; e < L.rp[i + 1]; ++e) {
-            A[i * n + L.col[e]] = -L.w64[e];
+            A[i * m + L.col[e]] = -L.w64[e];
             d += L.w64[e];
         }
-        A[i * n + i] = d;
+        A[i * m + i] = d;
     }
     __syncthreads();
     double f[1] = {0.0};
-    for (int t = tid; t < n * n; t += nt) f[0] += A[t] * A[t];
+    for (int t = tid; t < m * m; t += nt) f[0] += A[t] * A[t];
     block_sum<1>(f, red);
     const double fro = sqrt(f[0]);
-    const int m = n + (n & 1);  // players in the tournament (dummy index n if odd)
-    const int npair = m / 2;
-    for (int sweep = 0; sweep < 50; ++sweep) {
-        double o[1] = {0.0};
-        for (int t = tid; t < n * n; t += nt)
-            if (t / n != t % n) o[0] += A[t] * A[t];
-        block_sum<1>(o, red);
-        if (sqrt(o[0]) <= 1e-14 * fro) break;
-        for (int step = 0; step < m - 1; ++step) {
-            // pairs of this step and their rotations (from the current A)
-            for (int i = tid; i < npair; i += nt) {
-                int a, b;
-                if (i == 0) {
-                    a = 0;
-                    b = (step % (m - 1)) + 1;
-                } else {
-                    a = ((step + i) % (m - 1)) + 1;
-                    b = ((step - i + (m - 1)) % (m - 1)) + 1;
-                }
-                int p = min(a, b), q = max(a, b);
-                double c = 1.0, s = 0.0;
-                if (q < n) {
-                    double apq = A[p * n + q];
-                    if (apq != 0.0) {
-                        double tau = (A[q * n + q] - A[p * n + p]) / (2.0 * apq);
-                        double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                        c = 1.0 / sqrt(1.0 + tt * tt);
-                        s = tt * c;
-                    }
-                }
-                pr_p[i] = p;
-                pr_q[i] = (q < n) ? q : -1;
-                cs_c[i] = c;
-                cs_s[i] = s;
-            }
-            __syncthreads();
-            // rows p, q: A <- J^T A
-            for (int t = tid; t < npair * n; t += nt) {
-                int i = t / n, k = t % n;
-                int p = pr_p[i], q = pr_q[i];
-                if (q < 0 || cs_s[i] == 0.0) continue;
-                double c = cs_c[i], s = cs_s[i];
-                double x = A[p * n + k], y = A[q * n + k];
-                A[p * n + k] = c * x - s * y;
-                A[q * n + k] = s * x + c * y;
-            }
-            __syncthreads();
-            // columns p, q: A <- A J ; V <- V J
-            for (int t = tid; t < npair * n; t += nt) {
-                int i = t / n, k = t % n;
-                int p = pr_p[i], q = pr_q[i];
-                if (q < 0 || cs_s[i] == 0.0) continue;
-                double c = cs_c[i], s = cs_s[i];
-                double x = A[k * n + p], y = A[k * n + q];
-                A[k * n + p] = c * x - s * y;
-                A[k * n + q] = s * x + c * y;
-                x = V[k * n + p];
-                y = V[k * n + q];
-                V[k * n + p] = c * x - s * y;
-                V[k * n + q] = s * x + c * y;
-            }
-            __syncthreads();
-        }
-    }
-    for (int k = tid; k < n; k += nt) ev[k] = A[k * n + k];
-    __syncthreads();
-    if (tid == 0) {
-        for (int i = 0; i < n; ++i) idx[i] = i;
-        for (int i = 1; i < n; ++i) {
-            int t = idx[i];
-            int k = i - 1;
-            while (k >= 0 && ev[idx[k]] > ev[t]) {
-                idx[k + 1] = idx[k];
-                --k;
-            }
-            idx[k + 1] = t;
-        }
+    if (lds) jacobi_sweeps(dyn, dyn + m * m, m, fro, red, cs_c, cs_s, pr_p, pr_q);
+    else jacobi_sweeps(Jb.A, Vg, m, fro, red, cs_c, cs_s, pr_p, pr_q);
+    // ascending eigenvalues, the lower index first on ties
+    // (every index stays valid where a value is not a number)
+    for (int k = tid; k < n; k += nt) {
+        ev[k] = A[k * m + k];
+        idx[k] = k;
     }
     __syncthreads();
+    for (int k = tid; k < n; k += nt) {
+        const double e = ev[k];
+        int rank = 0;
+        for (int i = 0; i < n; ++i) rank += (ev[i] < e || (ev[i] == e && i < k)) ? 1 : 0;
+        idx[rank] = k;
+        Jb.ev[k] = e;
+    }
+    __syncthreads();
+    for (int k = tid; k < n; k += nt) Jb.idx[k] = idx[k];
     const double l2 = ev[idx[1]];
     double* y = (double*)L.buf0;
-    double* dots = ev + n;  // scratch: n entries after the eigenvalues
     for (int attempt = 0; attempt < 2; ++attempt) {
         // dots over the cluster
         for (int r = tid; r < n; r += nt) {
-            int k = idx[r];
+            const int k = idx[r];
             double d = 0.0;
             if (r >= 1 && fabs(ev[k] - l2) <= 1e-10 * fro) {
                 for (int i = 0; i < n; ++i) {
                     double z = attempt == 0 ? (double)i - 0.5 * (double)(n - 1)
                                             : hashed_uniform(seed, i) - 0.5;
-                    d += V[i * n + k] * z;
+                    d += V[i * m + k] * z;
                 }
             }
             dots[r] = d;
@@ -360,7 +380,7 @@ __global__ void __launch_bounds__(256) k_coarse_jobs(const CoarseJob* __restrict
         double acc[2] = {0.0, 0.0};
         for (int i = tid; i < n; i += nt) {
             double yi = 0.0;
-            for (int r = 1; r < n; ++r) yi += dots[r] * V[i * n + idx[r]];
+            for (int r = 1; r < n; ++r) yi += dots[r] * V[i * m + idx[r]];
             y[i] = yi;
             acc[0] += yi * yi;
             double z = attempt == 0 ? (double)i - 0.5 * (double)(n - 1) : hashed_uniform(seed, i) - 0.5;
@@ -374,9 +394,15 @@ __global__ void __launch_bounds__(256) k_coarse_jobs(const CoarseJob* __restrict
         }
         __syncthreads();
     }
-    // eigenvectors kept in LDS are left in Vg too (several-eigenpair starts read them)
-    if (n <= kDenseLds)
-        for (int t = tid; t < n * n; t += nt) Vg[t] = V[t];
+    // the eigenvectors are left in Vg with rows of n (several-eigenpair
+    // starts read them), from global memory by way of A
+    if (lds) {
+        for (int t = tid; t < n * n; t += nt) Vg[t] = V[(t / n) * m + t % n];
+    } else if (m != n) {
+        for (int t = tid; t < n * n; t += nt) Jb.A[t] = V[(t / n) * m + t % n];
+        __syncthreads();
+        for (int t = tid; t < n * n; t += nt) Vg[t] = Jb.A[t];
+    }
     if (tid == 0) {
         int mult = 0;
         for (int r = 1; r < n; ++r)
