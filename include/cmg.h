@@ -110,11 +110,13 @@ typedef struct {
                                     choices are cached per process by level shape, so results
                                     are reproducible within a process but may differ (within
                                     rounding) between processes.  0 (default): fixed rules. */
-    int32_t block_regs;          /* levels refined inside one workgroup: 0 (default) holds each
-                                    level's rows in registers for all its PI steps where a
-                                    layout fits (rows of at most 128 entries, those beyond
-                                    the layout's slots in an LDS list); -1 always reads the
-                                    CSR arrays.  Both give the same lambda to rounding. */
+    int32_t block_regs;          /* levels refined inside one workgroup: 0 (default) holds a level
+                                    of at most 64 vertices (most of up to 128) as a dense matrix
+                                    and takes sixteen PI steps per product with its sixteenth
+                                    power, a larger one's rows in registers for all its steps
+                                    where a layout fits (rows of at most 128 entries, those
+                                    beyond the layout's slots in an LDS list); -1 always reads
+                                    the CSR arrays.  All give the same lambda to rounding. */
     int32_t grid_stage;          /* FP64 levels refined by the whole grid with lanes per row:
                                     1 (default) copies each workgroup's rows, columns and
                                     weights to LDS once per level when they fit (at most 1024
@@ -183,7 +185,8 @@ typedef struct {
     double pi_ms;        /* device time of this level's refinement launch (grid levels) */
     double bytes_per_iter; /* algorithmic bytes of one PI step: 4(n+1)+nnz(4+s_v)+2 s_x n */
     int32_t block_waves;   /* in_block: wavefronts running the PI steps (0: all) */
-    int32_t block_regs;    /* in_block: rows per lane group held in registers (0: CSR reads) */
+    int32_t block_regs;    /* in_block: rows per lane group held in registers (0: CSR reads, or a
+                              level held as a dense matrix) */
     int32_t step;          /* 1 if refined with one launch per PI step (no grid barrier) */
     int32_t weights;       /* edge weights as the level's PI steps read them: 0 FP64, 1 FP32
                               (mixed-precision level, or an exact FP32 copy beside FP64

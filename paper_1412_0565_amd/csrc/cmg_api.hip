@@ -76,6 +76,7 @@ struct HostLevel {
     void* buf0 = nullptr;
     void* buf1 = nullptr;
     int32_t* part = nullptr;
+    int bdense = 0;          // single-workgroup level held as a dense matrix
     int bwaves = 0, bregs = 0, bslots = 0;  // single-workgroup level: waves, register rows, slots
     int step = 0;              // 1: refined with one launch per PI step
     int kfix = 0;              // fixed schedule: PI steps of this level (0: stopping test)
@@ -163,7 +164,8 @@ BlockPlan plan_block_regs(const HostLevel& L, int lds_budget) {
     const double slot_cost = 0.0125, lds_cost = 0.0012, lane_sum_cost = 0.02, list_trip_cost = 0.25;
     BlockPlan best;
     double best_cost = 0.0;
-    if (L.n < 1 || L.n > 65536 || !L.w32exact) return best;
+    if (L.n < 1 || L.n > 65536) return best;
+    const int list_bytes = L.w32exact ? 8 : 16;  // of an entry in the LDS list
     for (int W : {1, 2, 4, 8}) {
         for (int l = 0; l < kRegLayouts; ++l) {
             const int G = kRegLayoutG[l], E = kRegLayoutE[l];
@@ -171,7 +173,7 @@ BlockPlan plan_block_regs(const HostLevel& L, int lds_budget) {
             if (over > (int64_t)G * E) continue;
             if (over > 0) {
                 const int64_t list = std::min<int64_t>((int64_t)L.n * over, L.nnz);
-                if (16 * (int64_t)L.n + 8 * list > (int64_t)lds_budget) continue;
+                if (16 * (int64_t)L.n + list_bytes * list > (int64_t)lds_budget) continue;
             }
             const int groups = 64 * W / G;
             const int need = (L.n + groups - 1) / groups;
@@ -179,7 +181,11 @@ BlockPlan plan_block_regs(const HostLevel& L, int lds_budget) {
             if (R == 0) continue;
             if (W == 1 && (G != 1 || R != 1)) continue;
             const int64_t trips = (over + 2 * G - 1) / (2 * G);
-            const double cost = wave_cost[W] + R * E * slot_cost + W * R * E * lds_cost +
+            // slots done per row: rows are dealt out by length and a
+            // wavefront skips (in fours) those that none of its rows has;
+            // the largest layouts decode all their slots every step
+            const double done = R * E > 32 ? E : std::min<double>(E, L.nnz / (double)L.n / G + 2.0);
+            const double cost = wave_cost[W] + R * done * slot_cost + W * R * done * lds_cost +
                                 R * (bitlen((unsigned)G) - 1) * lane_sum_cost +
                                 (trips > 0 ? lane_sum_cost + trips * list_trip_cost : 0.0);
             if (best.regs == 0 || cost < best_cost) {
@@ -1115,6 +1121,17 @@ int fixed_steps(int k0, double beta, int j, int cap) {
     return c > (double)cap ? cap : (int)c;
 }
 
+// Single-workgroup levels held as dense matrices: up to 64 vertices always
+// (a step 0.03 us against 0.35 to 0.6 on register rows), up to 128 where
+// rows are short (0.07 against 0.5 to 0.8) or the level has more entries
+// than register rows take without many passes (n = 117, 7000 entries: 4.7
+// us on the CSR arrays).  The levels left between, of a few thousand
+// entries, stay on register rows with their list of long rows (0.9 us).
+bool dense_block_level(const HostLevel& L) {
+    if (L.n > kDenseBlockN || dense_block_lds(L.n) > refine_block_lds_budget()) return false;
+    return L.n <= 64 || L.nnz <= 16 * (int64_t)L.n || L.nnz > 4096;
+}
+
 cmg_status build_refine_plan(cmg_ctx* c) {
     Range range("cmg refinement plan");
     const int J = (int)c->lv.size() - 1;
@@ -1154,8 +1171,12 @@ cmg_status build_refine_plan(cmg_ctx* c) {
         HostLevel& L = c->lv[j];
         L.in_block = (j >= c->block_lo && j <= top) ? 1 : 0;
         L.stage = o.grid_stage != 0 ? 1 : 0;
-        L.bwaves = L.bregs = L.bslots = 0;
+        L.bwaves = L.bregs = L.bslots = L.bdense = 0;
         if (!L.in_block) continue;
+        if (o.block_regs >= 0 && dense_block_level(L)) {
+            L.bdense = 1;
+            continue;
+        }
         const BlockPlan p = o.block_regs < 0 ? BlockPlan{} : plan_block_regs(L, refine_block_lds_budget());
         if (p.regs > 0) {
             L.bwaves = p.waves;
@@ -1389,10 +1410,11 @@ cmg_status build_refine_plan(cmg_ctx* c) {
     c->brun_kind.clear();
     auto block_kind = [&](int j) {
         const HostLevel& L = c->lv[j];
+        if (L.bdense) return kBlockDense;
         if (L.bregs <= 0) return 0;
         int l = 0;
         while (l < kRegLayouts && !(kRegLayoutG[l] == L.lanes && kRegLayoutE[l] == L.bslots)) ++l;
-        return 1 + 3 * l + (bitlen((unsigned)L.bregs) - 1);
+        return 1 + 3 * l + (bitlen((unsigned)L.bregs) - 1) + (L.w32exact ? 0 : 3 * kRegLayouts);
     };
     for (int j = top; top >= 0 && j >= c->block_lo;) {
         const int kind = block_kind(j);

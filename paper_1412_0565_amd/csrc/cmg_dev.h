@@ -45,8 +45,9 @@ __device__ __forceinline__ T group_sum(T v, int G) {
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double v) {
     const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+    // (every lane of a row has a source under these controls: no old value)
+    const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffll), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, false);
     return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
@@ -93,6 +94,24 @@ __device__ __forceinline__ T sld(const T* p, I i) {
 template <typename T, typename I>
 __device__ __forceinline__ void sst(T* p, I i, T v) {
     ((CMG_AS_LDS T*)p)[i] = v;
+}
+
+// an entry of a vector of doubles or floats
+__device__ __forceinline__ double ld_any(const void* p, int fp32, int64_t i) {
+    return fp32 ? (double)gld((const float*)p, i) : gld((const double*)p, i);
+}
+
+// 1/x and 1/sqrt(x) to double rounding for normal x (hardware estimate and
+// two Newton steps: a quarter of the latency of a division or square root)
+__device__ __forceinline__ double fast_rcp(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(y, fma(-x, y, 1.0), y);
+    return fma(y, fma(-x, y, 1.0), y);
+}
+__device__ __forceinline__ double fast_rsq(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    return fma(0.5 * y, fma(-x * y, y, 1.0), y);
 }
 
 // Value of a lane, identical in every lane (needs that lane active).

@@ -210,8 +210,12 @@ constexpr int kRegLayoutG[kRegLayouts] = {1, 2, 4, 8, 1, 2, 4};
 constexpr int kRegLayoutE[kRegLayouts] = {8, 8, 8, 8, 16, 16, 16};
 // kind 0: CSR traversal on kBlockKernelThreads threads; 1 + 3 l + log2(R)
 // (layout l, R = 1, 2 or 4 rows per lane group): register rows on
-// kBlockRegsThreads threads.
-constexpr int kBlockKinds = 1 + 3 * kRegLayouts;
+// kBlockRegsThreads threads with FP32 weights, then the same with FP64
+// weights; last, levels of at most kDenseBlockN vertices as dense matrices.
+constexpr int kBlockDense = 1 + 2 * 3 * kRegLayouts;
+constexpr int kBlockKinds = kBlockDense + 1;
+constexpr int kDenseBlockN = 128;
+int dense_block_lds(int n);  // LDS bytes such a level needs
 hipError_t launch_block_jobs(const BlockJob* jobs, int njobs, int kind, hipStream_t s);
 // Job kernels are specialised by traversal (merge path or G lanes per
 // row) and precision: kind = 2 * t + fp32, t = 0 for the merge path, else

@@ -21,10 +21,6 @@ namespace cmg {
 
 namespace {
 
-__device__ __forceinline__ double ld_any(const void* p, int fp32, int64_t i) {
-    return fp32 ? (double)gld((const float*)p, i) : gld((const double*)p, i);
-}
-
 __device__ __forceinline__ double ld_agent(const double* p) {
     unsigned long long b =
         __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -215,19 +211,6 @@ __device__ __forceinline__ void pi_rows_dispatch(int G, const LevelDev& L, const
 
 // coarsest levels up to this size keep A and V in LDS (2 n^2 doubles)
 constexpr int kDenseLds = 48;
-
-// 1/x and 1/sqrt(x) to double rounding for normal x (hardware estimate and
-// two Newton steps: a quarter of the latency of a division or square root)
-__device__ __forceinline__ double fast_rcp(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-    y = fma(y, fma(-x, y, 1.0), y);
-    return fma(y, fma(-x, y, 1.0), y);
-}
-__device__ __forceinline__ double fast_rsq(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-    return fma(0.5 * y, fma(-x * y, y, 1.0), y);
-}
 
 // Sweeps of the Jacobi iteration in the parallel round-robin
 // ("tournament") order on the m x m matrix A (m even, row-major), rotations
@@ -422,951 +405,6 @@ __global__ void __launch_bounds__(256) k_coarse_jobs(const CoarseJob* __restrict
         *st = s0;
         fo->coarse_lambda2 = l2;
         fo->coarse_mult = mult;
-    }
-}
-
-// ------------------------------------------------ single-workgroup levels
-
-__device__ __forceinline__ size_t align8(size_t b) { return (b + 7) & ~(size_t)7; }
-
-// a load or store through the LDS view (LDS) or the global view
-template <bool LDS, typename T>
-__device__ __forceinline__ T ldx(const T* p, int i) {
-    if constexpr (LDS) return sld(p, i);
-    else return gld(p, i);
-}
-template <bool LDS, typename T>
-__device__ __forceinline__ void stx(T* p, int i, T v) {
-    if constexpr (LDS) sst(p, i, v);
-    else gst(p, i, v);
-}
-
-// Bytes of the LDS image of a level: two vectors, weights (FP32 when that
-// is exact), row pointers, columns (uint16 when n <= 65536).
-__device__ __forceinline__ size_t staged_bytes(const LevelDev& L, int w32, int col16) {
-    size_t b = align8(16 * (size_t)L.n);
-    b += align8((size_t)L.nnz * (w32 ? 4 : 8));
-    b += align8(4 * ((size_t)L.n + 1));
-    b += align8((size_t)L.nnz * (col16 ? 2 : 4));
-    return b;
-}
-
-// Levels up to this size run on one wavefront with no workgroup barrier.
-constexpr int kWaveRows = 256;
-
-// Sum of NV (<= 4) doubles over the active threads, identical in every
-// thread.  Wave mode: wave sum.  Workgroup mode: waves post their sums
-// (one barrier, alternating slots); each wave reads the posts with one LDS
-// access per lane, adds them within rows of 16 lanes and reads row q.
-template <int NV, bool WAVE>
-__device__ __forceinline__ void small_sum(double (&v)[NV], double* red, int& parity) {
-    const int lane = threadIdx.x & 63;
-    if constexpr (WAVE) {
-        // LDS writes of this step become visible to the other lanes
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int q = 0; q < NV; ++q) v[q] = group_sum_t<64>(v[q]);
-    } else {
-        const int wv = threadIdx.x >> 6;
-        const int nw = blockDim.x >> 6;
-        double* slot = red + parity * 64;
-#pragma unroll
-        for (int q = 0; q < NV; ++q) v[q] = group_sum_t<64>(v[q]);
-        if (lane == 0) {
-#pragma unroll
-            for (int q = 0; q < NV; ++q) slot[q * 16 + wv] = v[q];
-        }
-        __syncthreads();
-        double t = (lane < NV * 16 && (lane & 15) < nw) ? slot[lane] : 0.0;
-        t = group_sum_t<16>(t);
-#pragma unroll
-        for (int q = 0; q < NV; ++q) v[q] = read_lane(t, q * 16);
-        parity ^= 1;
-    }
-}
-
-// The four sums of a PI step over one wavefront, identical in every lane.
-// Lanes trade halves of their partials so that each exchange adds one
-// value per lane: after the two quad exchanges lane p of a quad holds the
-// quad sum of value 2 (p & 1) + (p >> 1); rotations of each row by 4 and 8
-// lanes, then the row and half swaps, complete the sums.
-__device__ __forceinline__ void wave_sum4(double (&v)[4]) {
-    const int lane = threadIdx.x & 63;
-    const bool odd = (lane & 1) != 0;
-    double k0 = odd ? v[2] : v[0];
-    double k1 = odd ? v[3] : v[1];
-    const double s0 = odd ? v[0] : v[2];
-    const double s1 = odd ? v[1] : v[3];
-    k0 += dpp_move<0xB1>(s0);
-    k1 += dpp_move<0xB1>(s1);
-    const bool hi = (lane & 2) != 0;
-    double k = hi ? k1 : k0;
-    k += dpp_move<0x4E>(hi ? k0 : k1);
-    k += dpp_move<0x124>(k);
-    k += dpp_move<0x128>(k);
-    k = pair_sum_rows<16>(k);
-    k = pair_sum_rows<32>(k);
-    v[0] = read_lane(k, 0);
-    v[2] = read_lane(k, 1);
-    v[1] = read_lane(k, 2);
-    v[3] = read_lane(k, 3);
-}
-
-// Sums of a PI step over the `nw` wavefronts that run the steps (the first
-// nw of the workgroup), identical in each of their lanes.  nw == 1: no
-// workgroup barrier.  Otherwise every such wave posts its four sums (one
-// barrier, alternating slots) and adds the posts within rows of 16 lanes.
-template <bool WAVE>
-__device__ __forceinline__ void step_sum4(double (&v)[4], double* red, int& parity, int nw) {
-    if constexpr (WAVE) {
-        // LDS writes of this step become visible to the other lanes
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        wave_sum4(v);
-    } else {
-        const int lane = threadIdx.x & 63;
-        const int wv = threadIdx.x >> 6;
-        double* slot = red + parity * 64;
-        wave_sum4(v);
-        if (lane == 0) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) slot[q * 16 + wv] = v[q];
-        }
-        __syncthreads();
-        double t = ((lane & 15) < nw) ? slot[lane] : 0.0;
-        t = group_sum_t<16>(t);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = read_lane(t, q * 16);
-        parity ^= 1;
-    }
-}
-
-// A product of a jump on a single-workgroup level, as in JumpOp.
-struct SmallJump {
-    bool first;
-    double be, cj;
-    double* jsum;
-    double* jback;
-};
-
-// One PI step (JUMP: one product of a jump) of a small level, rows shared by
-// `nthr` threads in G-lane groups.  Pointers are either all LDS (staged
-// modes) or all global.
-template <int G, bool W32, bool C16, bool LDS, bool JUMP>
-__device__ __forceinline__ void pi_small(int n, int nthr, const int32_t* rp, const void* colp,
-                                         const void* wp, double g, const double* win, double* wout,
-                                         double mu, double s, const SmallJump& sj, double (&acc)[4]) {
-    const int lane = threadIdx.x & (G - 1);
-    const int ngroups = nthr / G;
-    for (int i = (int)(threadIdx.x / G); i < n; i += ngroups) {
-        const int a = ldx<LDS>(rp, i), b = ldx<LDS>(rp, i + 1);
-        const double wi = ldx<LDS>(win, i);
-        double sum = wi, z = 0.0;
-        if constexpr (JUMP) {
-            if (!sj.first && lane == 0) {
-                sum = gld(sj.jsum, i);
-                z = ldx<LDS>(wout, i);
-            }
-        }
-        double t = 0.0;
-        int e = a + lane;
-        // four entries per trip: their column and value loads, then their
-        // gathers, are in flight together; the sum keeps the entry order
-        for (; e + 3 * G < b; e += 4 * G) {
-            int c[4];
-            double wt[4], x[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int f = e + q * G;
-                if constexpr (C16) c[q] = (int)ldx<LDS>((const uint16_t*)colp, f);
-                else c[q] = ldx<LDS>((const int32_t*)colp, f);
-                if constexpr (W32) wt[q] = (double)ldx<LDS>((const float*)wp, f);
-                else wt[q] = ldx<LDS>((const double*)wp, f);
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) x[q] = ldx<LDS>(win, c[q]);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) t += wt[q] * (x[q] - wi);
-        }
-        for (; e < b; e += G) {
-            int c;
-            double wt;
-            if constexpr (C16) c = (int)ldx<LDS>((const uint16_t*)colp, e);
-            else c = ldx<LDS>((const int32_t*)colp, e);
-            if constexpr (W32) wt = (double)ldx<LDS>((const float*)wp, e);
-            else wt = ldx<LDS>((const double*)wp, e);
-            t += wt * (ldx<LDS>(win, c) - wi);
-        }
-        t = group_sum_t<G>(t);
-        if (lane == 0) {
-            if constexpr (JUMP) {
-                const double y = (sj.first ? wi : 2.0 * wi) + sj.be * t - z;
-                stx<LDS>(wout, i, y);
-                gst(sj.jsum, i, sum + sj.cj * y);
-                if (sj.first) gst(sj.jback, i, wi);
-                acc[0] += wi * y;
-                acc[1] += y * y;
-                acc[2] += wi * wi;
-            } else {
-                const double x = (wi - mu) * s;
-                const double y = s * (g * (wi - mu) + t);
-                stx<LDS>(wout, i, y);
-                acc[0] += y;
-                acc[1] += y * y;
-                acc[2] += y * x;
-                acc[3] += x;
-            }
-        }
-    }
-}
-
-// the same for a run-time G
-template <bool W32, bool C16, bool LDS, bool JUMP>
-__device__ __forceinline__ void pi_small_any(int G, int n, int nthr, const int32_t* rp, const void* colp,
-                                             const void* wp, double g, const double* win, double* wout, double mu,
-                                             double s, const SmallJump& sj, double (&acc)[4]) {
-    switch (G) {
-        case 1: pi_small<1, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-        case 2: pi_small<2, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-        case 4: pi_small<4, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-        case 8: pi_small<8, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-        case 16: pi_small<16, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-        case 32: pi_small<32, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-        default: pi_small<64, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-    }
-}
-
-// Moments and samples of a jump, and its verdict.
-struct JumpLds {
-    double mom[kJumpMoments];
-    double dl[kJumpSamples];
-    int safe, next;
-};
-
-// After each barrier of the waves that run the steps: count it and tell the
-// idle waves that more follow.
-template <bool WAVE>
-__device__ __forceinline__ void small_bar(int* stop_flag, int& bar) {
-    ++bar;
-    if (!WAVE && threadIdx.x == 0) stop_flag[bar & 1] = 0;
-}
-
-template <bool WAVE>
-__device__ __forceinline__ void small_sync(double* red, int& parity, int* stop_flag, int& bar, int nw) {
-    double z[4] = {0.0, 0.0, 0.0, 0.0};
-    step_sum4<WAVE>(z, red, parity, nw);
-    small_bar<WAVE>(stop_flag, bar);
-}
-
-// Mean and norm of b0, each entry written by the thread that reads it here.
-template <bool WAVE, bool LDS>
-__device__ __forceinline__ void small_normalise(int n, int nact, const double* b0, double* red, int& parity,
-                                                int* stop_flag, int& bar, int nw, double& mu, double& s) {
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int i = threadIdx.x; i < n; i += nact) v[0] += ldx<LDS>(b0, i);
-    step_sum4<WAVE>(v, red, parity, nw);
-    small_bar<WAVE>(stop_flag, bar);
-    mu = v[0] / (double)n;
-    v[0] = v[1] = v[2] = v[3] = 0.0;
-    for (int i = threadIdx.x; i < n; i += nact) {
-        const double d = ldx<LDS>(b0, i) - mu;
-        v[0] += d * d;
-    }
-    step_sum4<WAVE>(v, red, parity, nw);
-    small_bar<WAVE>(stop_flag, bar);
-    s = 1.0 / sqrt(v[0]);
-}
-
-// Verdict on a jump whose products are done, the same in every running
-// thread; the moments are in js.
-template <bool WAVE>
-__device__ __forceinline__ bool small_jump_end(int K, int d, double tol, JumpLds* js, double* red, int& parity,
-                                               int* stop_flag, int& bar, int nw, int* more, int* hold) {
-    if (tol < 0.0) {
-        small_sync<WAVE>(red, parity, stop_flag, bar, nw);
-        return jump_verdict(K, 0, 0, true, more, hold);
-    }
-    small_sync<WAVE>(red, parity, stop_flag, bar, nw);
-    // a sample per running thread (at least 128, at most kJumpSamples)
-    const int ns = min(kJumpSamples, max(64 * nw, 128));
-    for (int q = threadIdx.x; q < ns; q += 64 * nw)
-        js->dl[q] = jump_delta(js->mom, 2 * d + 1, jump_sample(q, ns, K));
-    small_sync<WAVE>(red, parity, stop_flag, bar, nw);
-    if (threadIdx.x < 64) {
-        int safe, next;
-        jump_judge(js->dl, ns, K, tol, &safe, &next);
-        if (threadIdx.x == 0) {
-            js->safe = safe;
-            js->next = next;
-        }
-    }
-    small_sync<WAVE>(red, parity, stop_flag, bar, nw);
-    return jump_verdict(K, js->safe, js->next, false, more, hold);
-}
-
-struct SmallIn {
-    const void* cbuf;  // final vector of the coarser level
-    int cfp32;
-    int uniform;
-    double cm, cs;     // its transform (v - cm) * cs
-    uint64_t seed;
-    double tol;
-    int maxit;
-};
-
-// Rows of a small level read from its CSR arrays every step (an LDS image
-// or global memory), in G-lane groups with G = L.lanes.
-// Rows of a small level held in registers for all its steps: each G-lane
-// group owns rows grp + r * ngroups (r < R) and each lane E entries of
-// every such row (entry a + lane + m G in slot m; columns as uint16 pairs,
-// weights as FP32, which the level's weights equal exactly), so a step is
-// one round of independent gathers from the LDS vector.  Unused slots point
-// at the row's own vertex with weight 0 and add an exact zero, which keeps
-// the sums bit for bit those of the CSR traversal with the same G.
-// A row longer than G E keeps its further entries (column, FP32 weight)
-// in an LDS list; the lanes take them as slots E, E + 1, ... of the same
-// stride, so each lane still sums its entries in CSR order.
-template <int G, int R, int E>
-struct RegRows {
-    uint32_t c2[R][E / 2];
-    float w[R][E];
-    int row[R];
-    int ooff[R], ocnt[R];  // the row's entries beyond G E: LDS list offset and count
-    const uint64_t* ovl;
-    int n;
-    double g;
-
-    // ov: LDS list of ovcap entries, filled from *ofill (zero before the
-    // first call of the level); a list that would overflow sets *bad
-    __device__ __forceinline__ void load(const LevelDev& L, int nact, int* bad, uint64_t* ov, int ovcap, int* ofill) {
-        n = L.n;
-        g = L.g;
-        ovl = ov;
-        const int lane = (int)threadIdx.x & (G - 1);
-        const int lead = ((int)threadIdx.x & (kWave - 1)) & ~(G - 1);
-        const int ngroups = nact / G;
-        const int grp = (int)threadIdx.x / G;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int i = grp + r * ngroups;
-            row[r] = i < n ? i : -1;
-            int a = 0, b = 0;
-            if (i < n) {
-                a = gld(L.rp, i);
-                b = gld(L.rp, i + 1);
-            }
-            // the same count in every lane of the group; its first lane
-            // takes the list space for all of them
-            int extra = max(b - a - G * E, 0);
-            int off = 0;
-            if (extra > 0 && lane == 0) off = atomicAdd(ofill, extra);
-            off = __shfl(off, lead, kWave);
-            if (extra > 0 && (off < 0 || off > ovcap - extra)) {
-                if (lane == 0) *bad = 1;
-                extra = 0;
-            }
-            ooff[r] = off;
-            ocnt[r] = extra;
-            for (int q = lane; q < extra; q += G) {
-                const int e = a + G * E + q;
-                const uint64_t wb = __float_as_uint((float)gld(L.w64, e));
-                sst(ov, off + q, (uint64_t)(uint32_t)gld(L.col, e) | (wb << 32));
-            }
-            const uint32_t self = i < n ? (uint32_t)i : 0u;
-#pragma unroll
-            for (int m = 0; m < E; ++m) {
-                const int e = a + lane + m * G;
-                uint32_t cv = self;
-                float wv = 0.0f;
-                if (e < b) {
-                    cv = (uint32_t)gld(L.col, e);
-                    wv = (float)gld(L.w64, e);
-                }
-                if (m & 1) c2[r][m >> 1] |= cv << 16;
-                else c2[r][m >> 1] = cv;
-                w[r][m] = wv;
-            }
-        }
-        // the list entries are read back by the lanes of the group that
-        // wrote them, in the same wavefront
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-
-    // sum over row r's entries a (w_k - w_i), in every lane of the group
-    __device__ __forceinline__ double row_sum(int r, const double* win, double wi) {
-        const int lane = (int)threadIdx.x & (G - 1);
-        const int i = row[r];
-        if constexpr (R * E > 32) {
-            // decode the columns and widen the weights every step:
-            // hoisted out of the step loop they would not fit
-#pragma unroll
-            for (int q = 0; q < E / 2; ++q) asm volatile("" : "+v"(c2[r][q]));
-#pragma unroll
-            for (int q = 0; q < E; ++q) asm volatile("" : "+v"(w[r][q]));
-        }
-        double x[E];
-#pragma unroll
-        for (int m = 0; m < E; ++m) x[m] = sld(win, (int)((m & 1) ? (c2[r][m >> 1] >> 16) : (c2[r][m >> 1] & 0xffffu)));
-        double t = 0.0;
-#pragma unroll
-        for (int m = 0; m < E; ++m) t += (double)w[r][m] * (x[m] - wi);
-        // entries beyond G E, two per trip; the second of a trip past
-        // the row's end is its own vertex with weight 0 (an exact zero)
-        for (int q = lane; q < ocnt[r]; q += 2 * G) {
-            const uint64_t p0 = sld(ovl, ooff[r] + q);
-            const uint64_t p1 = q + G < ocnt[r] ? sld(ovl, ooff[r] + q + G) : (uint64_t)(uint32_t)i;
-            const double x0 = sld(win, (int)(uint32_t)p0), x1 = sld(win, (int)(uint32_t)p1);
-            t += (double)__uint_as_float((uint32_t)(p0 >> 32)) * (x0 - wi);
-            t += (double)__uint_as_float((uint32_t)(p1 >> 32)) * (x1 - wi);
-        }
-        return group_sum_t<G>(t);
-    }
-
-    __device__ __forceinline__ void step(const double* win, double* wout, double mu, double s, double (&acc)[4]) {
-        const int lane = (int)threadIdx.x & (G - 1);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int i = row[r];
-            const double wi = sld(win, i < 0 ? 0 : i);
-            const double t = row_sum(r, win, wi);
-            if (lane == 0 && i >= 0) {
-                const double xv = (wi - mu) * s;
-                const double y = s * (g * (wi - mu) + t);
-                sst(wout, i, y);
-                acc[0] += y;
-                acc[1] += y * y;
-                acc[2] += y * xv;
-                acc[3] += xv;
-            }
-        }
-    }
-
-    // one product of a jump, as in JumpOp, with the jump's sum and the
-    // vector before it in registers
-    __device__ __forceinline__ void product(const double* win, double* wout, bool first, double be, double cj,
-                                            double (&jsum)[R], double (&jback)[R], double (&acc)[4]) {
-        const int lane = (int)threadIdx.x & (G - 1);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int i = row[r];
-            const double wi = sld(win, i < 0 ? 0 : i);
-            const double z = sld(wout, i < 0 ? 0 : i);
-            const double t = row_sum(r, win, wi);
-            const double y = (first ? wi : 2.0 * wi - z) + be * t;
-            if (first) jback[r] = jsum[r] = wi;
-            jsum[r] += cj * y;
-            if (lane == 0 && i >= 0) {
-                sst(wout, i, y);
-                acc[0] += wi * y;
-                acc[1] += y * y;
-                acc[2] += wi * wi;
-            }
-        }
-    }
-};
-
-// Prolongation, deflation, normalisation and PI steps of one small level
-// read from its CSR arrays.  MODE 0: LDS image, one wavefront; 1: LDS
-// image, whole workgroup; 2: global memory, whole workgroup.
-template <int MODE, bool W32, bool C16>
-__device__ void small_level(const LevelDev& L, const SmallIn& in, double* lds, double* red, int& parity,
-                            int* stop_flag, JumpLds* js, int nw_run, LevelState& out) {
-    constexpr bool WAVE = (MODE == 0);
-    constexpr bool LDS = (MODE != 2);
-    const int n = L.n;
-    const int nthr = WAVE ? 64 : (int)blockDim.x;
-    double* b0;
-    double* b1;
-    const int32_t* rp;
-    const void* colp;
-    const void* wp;
-    if constexpr (MODE != 2) {
-        char* p = (char*)lds;
-        b0 = (double*)p;
-        b1 = b0 + n;
-        p += align8(16 * (size_t)n);
-        wp = p;
-        p += align8((size_t)L.nnz * (W32 ? 4 : 8));
-        rp = (const int32_t*)p;
-        p += align8(4 * ((size_t)n + 1));
-        colp = p;
-    } else {
-        b0 = (double*)L.buf0;
-        b1 = (double*)L.buf1;
-        rp = L.rp;
-        colp = L.col;
-        wp = L.w64;
-    }
-    double sum[1] = {0.0};
-    if (in.uniform) {
-        for (int i = threadIdx.x; i < n; i += nthr) {
-            const double v = hashed_uniform(in.seed, i) - 0.5;
-            stx<LDS>(b0, i, v);
-            sum[0] += v;
-        }
-    } else {
-        for (int i = threadIdx.x; i < n; i += nthr) {
-            const double v = (ld_any(in.cbuf, in.cfp32, gld(L.agg, i)) - in.cm) * in.cs;
-            stx<LDS>(b0, i, v);
-            sum[0] += v;
-        }
-    }
-    small_sum<1, WAVE>(sum, red, parity);
-    double mu = sum[0] / (double)n;
-    double ss[1] = {0.0};
-    for (int i = threadIdx.x; i < n; i += nthr) {
-        const double d = ldx<LDS>(b0, i) - mu;
-        ss[0] += d * d;
-    }
-    small_sum<1, WAVE>(ss, red, parity);
-    double s = 1.0 / sqrt(ss[0]);
-    int cur = 0, k = 0, hit = 0;
-    double utv = 0.0, pmu = mu, ps = s;
-    // The PI steps run on the first `nw` wavefronts; the others only keep
-    // the barrier count: after each barrier they read the flag left after
-    // the one before it, and the running waves end with one more barrier.
-    const int nw = WAVE ? 1 : nw_run;
-    const int nact = 64 * nw;
-    // wave-uniform test, taken as a scalar branch
-    if (WAVE || __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < nw) {
-        const bool jumps = L.jmom != nullptr && (in.tol < 0.0 || in.tol >= kJumpTolMin);
-        int bar = 0;              // barriers passed
-        int since = 0, hold = 0;  // plain steps since the last jump, and to take before the next estimate
-        while (true) {
-            const double* win = cur ? b1 : b0;
-            double* wout = cur ? b0 : b1;
-            double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            pi_small_any<W32, C16, LDS, false>(L.lanes, n, nact, rp, colp, wp, L.g, win, wout, mu, s, SmallJump{}, acc);
-            step_sum4<WAVE>(acc, red, parity, nw);
-            ++bar;
-            const double mu2 = acc[0] / (double)n;
-            const double s2 = 1.0 / sqrt(acc[1] - acc[0] * mu2);
-            const double utvp = utv;
-            utv = s2 * (acc[2] - mu2 * acc[3]);
-            ++k;
-            cur ^= 1;
-            pmu = mu;
-            ps = s;
-            mu = mu2;
-            s = s2;
-            bool stop = !(utv < 1.0 - in.tol);
-            if (!stop && k >= in.maxit) {
-                hit = 1;
-                stop = true;
-            }
-            if (!WAVE && threadIdx.x == 0) stop_flag[bar & 1] = stop ? 1 : 0;
-            if (stop) break;
-            if (hold > 0) {
-                --hold;
-                continue;
-            }
-            if (!jumps || !jump_due(++since)) continue;
-            const double r = 1.0 / (s * L.g);
-            int K = jump_plan(utv, utvp, in.tol, r, in.maxit - k - 1);
-            while (K > 0) {
-                const int d = jump_products(K);
-                SmallJump sj;
-                sj.jsum = L.jsum;
-                sj.jback = L.jback;
-                sj.cj = 2.0 * (double)K / (double)(K + 1);
-                for (int j = 0; j < d; ++j) {
-                    sj.first = j == 0;
-                    sj.be = (j == 0 ? 2.0 : 4.0) / L.g;
-                    double sum4[4] = {0.0, 0.0, 0.0, 0.0};
-                    pi_small_any<W32, C16, LDS, true>(L.lanes, n, nact, rp, colp, wp, L.g, cur ? b1 : b0,
-                                                      cur ? b0 : b1, mu, s, sj, sum4);
-                    step_sum4<WAVE>(sum4, red, parity, nw);
-                    small_bar<WAVE>(stop_flag, bar);
-                    if (threadIdx.x == 0) jump_moments(js->mom, j, sum4[0], sum4[1], sum4[2]);
-                    sj.cj = jump_coef(sj.cj, K, j + 1);
-                    cur ^= 1;
-                }
-                int more = 0;
-                const bool keep = small_jump_end<WAVE>(K, d, in.tol, js, red, parity, stop_flag, bar, nw, &more, &hold);
-                const double* src = keep ? L.jsum : L.jback;
-                for (int i = threadIdx.x; i < n; i += nact) stx<LDS>(b0, i, gld(src, i));
-                if (keep) {
-                    k += K;
-                    small_normalise<WAVE, LDS>(n, nact, b0, red, parity, stop_flag, bar, nw, mu, s);
-                } else {
-                    small_sync<WAVE>(red, parity, stop_flag, bar, nw);
-                }
-                cur = 0;
-                since = 0;
-                K = more > 0 ? jump_steps((double)more, r, in.maxit - k - 1) : 0;
-            }
-        }
-        if constexpr (!WAVE) __syncthreads();
-    } else {
-        // the flag left after barrier q - 1 tells whether barrier q is the
-        // closing one; the slot parity follows the barriers, as in the
-        // running waves
-        for (int q = 1;; ++q) {
-            __syncthreads();
-            if (q > 1 && stop_flag[(q - 1) & 1]) break;
-            parity ^= 1;
-        }
-        return;  // the state is kept by thread 0
-    }
-    int fin = cur;
-    if constexpr (MODE != 2) {
-        // the LDS vectors are discarded: final vector to buf0, previous to buf1
-        const double* src = cur ? b1 : b0;
-        const double* prv = cur ? b0 : b1;
-        double* g0 = (double*)L.buf0;
-        double* g1 = (double*)L.buf1;
-        for (int i = threadIdx.x; i < n; i += nact) {
-            gst(g0, i, sld(src, i));
-            gst(g1, i, sld(prv, i));
-        }
-        fin = 0;
-    }
-    out.mu = mu;
-    out.s = s;
-    out.mu_prev = pmu;
-    out.s_prev = ps;
-    out.utv = utv;
-    out.margin = utv - (1.0 - in.tol);
-    out.fin = fin;
-    out.k = k;
-    out.maxit = hit;
-    out.err = 0;
-    out.ticks = 0;
-}
-
-// Levels jhi down to jlo (all FP64, small) refined inside one workgroup:
-// prolongation, deflation, normalisation and every PI step separated only
-// by workgroup (or wavefront) barriers, so thousands of steps cost no
-// launches.  A level whose CSR and two vectors fit in `lds_budget` bytes
-// is first copied to LDS (columns as uint16 when n <= 65536, weights as
-// FP32 when that is exact) and its steps touch no global memory; levels of
-// at most kWaveRows vertices then run on a single wavefront, larger ones on
-// LevelDev::bwaves wavefronts (0: all).  Larger levels stream from global
-// memory (L2).  The final vector of each level goes to buf0 (its
-// predecessor to buf1).
-__global__ void __launch_bounds__(kBlockKernelThreads)
-    k_block_jobs(const BlockJob* __restrict__ jobs, int lds_budget) {
-    extern __shared__ double lds[];
-    __shared__ double red[2 * 64];
-    __shared__ double s_cm, s_cs;
-    __shared__ int s_cfin;
-    __shared__ int s_stop[2];
-    __shared__ JumpLds s_jump;
-    const BlockJob Jb = jobs[blockIdx.x];
-    const LevelDev* __restrict__ lv = Jb.lv;
-    int parity = 0;
-    if (threadIdx.x == 0 && !Jb.uniform) {
-        LevelState c = Jb.st[Jb.jhi + 1];
-        s_cm = c.mu;
-        s_cs = c.s;
-        s_cfin = c.fin;
-    }
-    __syncthreads();
-    for (int j = Jb.jhi; j >= Jb.jlo; --j) {
-        const long long t_start = wall_clock64();
-        const LevelDev L = lv[j];
-        const int n = L.n;
-        const int nwmax = (int)(blockDim.x >> 6);
-        const int nw = L.bwaves > 0 ? min(L.bwaves, nwmax) : (n <= kWaveRows ? 1 : nwmax);
-        const int c16 = (n <= 65536) ? 1 : 0;
-        int w32 = 0;
-        size_t need = staged_bytes(L, 0, c16);
-        if (need > (size_t)lds_budget && L.w32exact) {
-            w32 = 1;
-            need = staged_bytes(L, 1, c16);
-        }
-        const bool staged = need <= (size_t)lds_budget;
-        const int mode = staged ? (nw == 1 ? 0 : 1) : 2;
-        if (staged) {
-            char* p = (char*)lds + align8(16 * (size_t)n);
-            void* wdst = p;
-            p += align8((size_t)L.nnz * (w32 ? 4 : 8));
-            int32_t* rdst = (int32_t*)p;
-            p += align8(4 * ((size_t)n + 1));
-            void* cdst = p;
-            for (int i = threadIdx.x; i <= n; i += blockDim.x) sst(rdst, i, gld(L.rp, i));
-            for (int e = threadIdx.x; e < (int)L.nnz; e += blockDim.x) {
-                const int cv = gld(L.col, e);
-                const double wv = gld(L.w64, e);
-                if (c16) sst((uint16_t*)cdst, e, (uint16_t)cv);
-                else sst((int32_t*)cdst, e, (int32_t)cv);
-                if (w32) sst((float*)wdst, e, (float)wv);
-                else sst((double*)wdst, e, wv);
-            }
-            __syncthreads();
-        }
-        SmallIn in;
-        in.uniform = (Jb.uniform && j == Jb.jhi) ? 1 : 0;
-        if (!in.uniform) {
-            const LevelDev C = lv[j + 1];
-            in.cbuf = s_cfin ? C.buf1 : C.buf0;
-            in.cfp32 = C.fp32;
-        } else {
-            in.cbuf = nullptr;
-            in.cfp32 = 0;
-        }
-        in.cm = s_cm;
-        in.cs = s_cs;
-        in.seed = Jb.seed;
-        in.tol = L.kfix > 0 ? -1.0 : Jb.tol;  // a fixed schedule never passes the test
-        in.maxit = L.kfix > 0 ? L.kfix : Jb.maxit;
-        LevelState o;
-        if (mode == 0) {
-            if (threadIdx.x < 64) {
-                if (w32) {
-                    if (c16) small_level<0, true, true>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
-                    else small_level<0, true, false>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
-                } else {
-                    if (c16) small_level<0, false, true>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
-                    else small_level<0, false, false>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
-                }
-            }
-        } else if (mode == 1) {
-            if (w32) {
-                if (c16) small_level<1, true, true>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
-                else small_level<1, true, false>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
-            } else {
-                if (c16) small_level<1, false, true>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
-                else small_level<1, false, false>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
-            }
-        } else {
-            small_level<2, false, false>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
-        }
-        if (threadIdx.x == 0) {
-            o.ticks = wall_clock64() - t_start;
-            Jb.st[j] = o;
-            s_cm = o.mu;
-            s_cs = o.s;
-            s_cfin = o.fin;
-        }
-        __syncthreads();
-    }
-}
-
-// One level on register rows with both vectors in LDS (and the entries of
-// rows longer than the layout in the LDS list ov of ovcap entries, filled
-// from *ofill).  nw == 1: on wavefront 0 alone with no workgroup barrier
-// (the caller keeps the other waves out); else the first nw waves run the
-// steps and the others keep the barrier count as in the CSR traversal.
-template <int G, int R, int E>
-__device__ void reg_level(const LevelDev& L, const SmallIn& in, double* b0, double* b1, uint64_t* ov, int ovcap,
-                          int* ofill, double* red, int& parity, int* stop_flag, JumpLds* js, int* bad, int nw,
-                          LevelState& out) {
-    const bool wave = (nw == 1);
-    const int n = L.n;
-    const int nthr = wave ? 64 : (int)blockDim.x;
-    double sum[1] = {0.0};
-    if (in.uniform) {
-        for (int i = threadIdx.x; i < n; i += nthr) {
-            const double v = hashed_uniform(in.seed, i) - 0.5;
-            sst(b0, i, v);
-            sum[0] += v;
-        }
-    } else {
-        for (int i = threadIdx.x; i < n; i += nthr) {
-            const double v = (ld_any(in.cbuf, in.cfp32, gld(L.agg, i)) - in.cm) * in.cs;
-            sst(b0, i, v);
-            sum[0] += v;
-        }
-    }
-    if (wave) small_sum<1, true>(sum, red, parity);
-    else small_sum<1, false>(sum, red, parity);
-    double mu = sum[0] / (double)n;
-    double ss[1] = {0.0};
-    for (int i = threadIdx.x; i < n; i += nthr) {
-        const double d = sld(b0, i) - mu;
-        ss[0] += d * d;
-    }
-    if (wave) small_sum<1, true>(ss, red, parity);
-    else small_sum<1, false>(ss, red, parity);
-    double s = 1.0 / sqrt(ss[0]);
-    int cur = 0, k = 0, hit = 0;
-    double utv = 0.0, pmu = mu, ps = s;
-    const int nact = 64 * nw;
-    if (!(wave || __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < nw)) {
-        // counts the barriers along, as in the CSR traversal
-        for (int q = 1;; ++q) {
-            __syncthreads();
-            if (q > 1 && stop_flag[(q - 1) & 1]) break;
-            parity ^= 1;
-        }
-        return;  // the state is kept by thread 0
-    }
-    RegRows<G, R, E> rows;
-    rows.load(L, nact, bad, ov, ovcap, ofill);
-    const bool jumps = L.jmom != nullptr && (in.tol < 0.0 || in.tol >= kJumpTolMin);
-    int bar = 0;              // barriers passed
-    int since = 0, hold = 0;  // plain steps since the last jump, and to take before the next estimate
-    while (true) {
-        const double* win = cur ? b1 : b0;
-        double* wout = cur ? b0 : b1;
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        rows.step(win, wout, mu, s, acc);
-        if (wave) step_sum4<true>(acc, red, parity, 1);
-        else step_sum4<false>(acc, red, parity, nw);
-        ++bar;
-        const double mu2 = acc[0] / (double)n;
-        const double s2 = 1.0 / sqrt(acc[1] - acc[0] * mu2);
-        const double utvp = utv;
-        utv = s2 * (acc[2] - mu2 * acc[3]);
-        ++k;
-        cur ^= 1;
-        pmu = mu;
-        ps = s;
-        mu = mu2;
-        s = s2;
-        bool stop = !(utv < 1.0 - in.tol);
-        if (!stop && k >= in.maxit) {
-            hit = 1;
-            stop = true;
-        }
-        if (!wave && threadIdx.x == 0) stop_flag[bar & 1] = stop ? 1 : 0;
-        if (stop) break;
-        if (hold > 0) {
-            --hold;
-            continue;
-        }
-        if (!jumps || !jump_due(++since)) continue;
-        const double r = 1.0 / (s * L.g);
-        int K = jump_plan(utv, utvp, in.tol, r, in.maxit - k - 1);
-        while (K > 0) {
-            const int d = jump_products(K);
-            double cj = 2.0 * (double)K / (double)(K + 1);
-            double jsum[R], jback[R];
-            for (int j = 0; j < d; ++j) {
-                double sum4[4] = {0.0, 0.0, 0.0, 0.0};
-                rows.product(cur ? b1 : b0, cur ? b0 : b1, j == 0, (j == 0 ? 2.0 : 4.0) / L.g, cj, jsum, jback, sum4);
-                if (wave) step_sum4<true>(sum4, red, parity, 1);
-                else step_sum4<false>(sum4, red, parity, nw);
-                if (wave) small_bar<true>(stop_flag, bar);
-                else small_bar<false>(stop_flag, bar);
-                if (threadIdx.x == 0) jump_moments(js->mom, j, sum4[0], sum4[1], sum4[2]);
-                cj = jump_coef(cj, K, j + 1);
-                cur ^= 1;
-            }
-            int more = 0;
-            const bool keep =
-                wave ? small_jump_end<true>(K, d, in.tol, js, red, parity, stop_flag, bar, 1, &more, &hold)
-                     : small_jump_end<false>(K, d, in.tol, js, red, parity, stop_flag, bar, nw, &more, &hold);
-#pragma unroll
-            for (int q = 0; q < R; ++q)
-                if (((int)threadIdx.x & (G - 1)) == 0 && rows.row[q] >= 0) sst(b0, rows.row[q], keep ? jsum[q] : jback[q]);
-            if (wave) small_sync<true>(red, parity, stop_flag, bar, 1);
-            else small_sync<false>(red, parity, stop_flag, bar, nw);
-            if (keep) {
-                k += K;
-                if (wave) small_normalise<true, true>(n, 64, b0, red, parity, stop_flag, bar, 1, mu, s);
-                else small_normalise<false, true>(n, nact, b0, red, parity, stop_flag, bar, nw, mu, s);
-            }
-            cur = 0;
-            since = 0;
-            K = more > 0 ? jump_steps((double)more, r, in.maxit - k - 1) : 0;
-        }
-    }
-    if (!wave) __syncthreads();
-    // the LDS vectors are discarded: final vector to buf0, previous to buf1
-    const double* src = cur ? b1 : b0;
-    const double* prv = cur ? b0 : b1;
-    double* g0 = (double*)L.buf0;
-    double* g1 = (double*)L.buf1;
-    for (int i = threadIdx.x; i < n; i += nact) {
-        gst(g0, i, sld(src, i));
-        gst(g1, i, sld(prv, i));
-    }
-    if (wave) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    out.mu = mu;
-    out.s = s;
-    out.mu_prev = pmu;
-    out.s_prev = ps;
-    out.utv = utv;
-    out.margin = utv - (1.0 - in.tol);
-    out.fin = 0;
-    out.k = k;
-    out.maxit = hit;
-    out.err = *bad;
-    out.ticks = 0;
-}
-
-// Levels jhi down to jlo refined inside one workgroup on register rows of
-// G lanes per row, R rows per lane group and E slots per lane and row
-// (every level of the job has that layout and LevelDev::bwaves waves;
-// FP32-exact weights; rows longer than G E keep the rest in the LDS left
-// after the two vectors).  A level whose layout does not fit is skipped
-// with err = 2 in its state; err = 1 if the entries beyond the layout do
-// not fit the LDS left.
-template <int G, int R, int E>
-__global__ void __launch_bounds__(kBlockRegsThreads)
-    k_block_regs(const BlockJob* __restrict__ jobs, int lds_budget) {
-    extern __shared__ double lds[];
-    __shared__ double red[2 * 64];
-    __shared__ double s_cm, s_cs;
-    __shared__ int s_cfin;
-    __shared__ int s_stop[2];
-    __shared__ JumpLds s_jump;
-    __shared__ int s_bad;
-    __shared__ int s_ofill;
-    const BlockJob Jb = jobs[blockIdx.x];
-    const LevelDev* __restrict__ lv = Jb.lv;
-    int parity = 0;
-    if (threadIdx.x == 0 && !Jb.uniform) {
-        LevelState c = Jb.st[Jb.jhi + 1];
-        s_cm = c.mu;
-        s_cs = c.s;
-        s_cfin = c.fin;
-    }
-    __syncthreads();
-    for (int j = Jb.jhi; j >= Jb.jlo; --j) {
-        const long long t_start = wall_clock64();
-        const LevelDev L = lv[j];
-        const int n = L.n;
-        const int nw = max(1, min(L.bwaves, (int)(blockDim.x >> 6)));
-        const bool fits = L.lanes == G && L.bregs == R && L.bslots == E && L.w32exact && n >= 1 && n <= 65536 &&
-                          16 * (size_t)n <= (size_t)lds_budget && n <= R * (64 * nw / G) &&
-                          (nw > 1 || (G == 1 && R == 1));
-        if (threadIdx.x == 0) {
-            s_bad = 0;
-            s_ofill = 0;
-        }
-        // list of the entries beyond the layout: the LDS left after the vectors
-        uint64_t* ov = (uint64_t*)(lds + 2 * (size_t)n);
-        const int ovcap = fits ? (int)(((size_t)lds_budget - 16 * (size_t)n) / 8) : 0;
-        SmallIn in;
-        in.uniform = (Jb.uniform && j == Jb.jhi) ? 1 : 0;
-        if (!in.uniform) {
-            const LevelDev C = lv[j + 1];
-            in.cbuf = s_cfin ? C.buf1 : C.buf0;
-            in.cfp32 = C.fp32;
-        } else {
-            in.cbuf = nullptr;
-            in.cfp32 = 0;
-        }
-        in.cm = s_cm;
-        in.cs = s_cs;
-        in.seed = Jb.seed;
-        in.tol = L.kfix > 0 ? -1.0 : Jb.tol;  // a fixed schedule never passes the test
-        in.maxit = L.kfix > 0 ? L.kfix : Jb.maxit;
-        LevelState o{};
-        if (!fits) {
-            o.err = 2;
-        } else if (nw == 1) {
-            if (threadIdx.x < 64)
-                reg_level<G, R, E>(L, in, lds, lds + n, ov, ovcap, &s_ofill, red, parity, s_stop, &s_jump, &s_bad, 1, o);
-        } else {
-            reg_level<G, R, E>(L, in, lds, lds + n, ov, ovcap, &s_ofill, red, parity, s_stop, &s_jump, &s_bad, nw, o);
-        }
-        if (threadIdx.x == 0) {
-            o.ticks = wall_clock64() - t_start;
-            Jb.st[j] = o;
-            s_cm = o.mu;
-            s_cs = o.s;
-            s_cfin = o.fin;
-        }
-        __syncthreads();
     }
 }
 
@@ -2704,61 +1742,6 @@ hipError_t launch_coarse_jobs(const CoarseJob* jobs, int njobs, hipStream_t s) {
     const size_t shmem = sizeof(double) * 2 * kDenseLds * kDenseLds;
     hipLaunchKernelGGL(k_coarse_jobs, dim3(njobs), dim3(256), shmem, s, jobs);
     return hipGetLastError();
-}
-
-namespace {
-template <int G, int E>
-const void* block_regs_kernel(int ri) {
-    return ri == 0 ? (const void*)k_block_regs<G, 1, E> : ri == 1 ? (const void*)k_block_regs<G, 2, E>
-                                                                 : (const void*)k_block_regs<G, 4, E>;
-}
-// kind 0: CSR traversal; 1 + 3 l + log2(R): register rows of layout l
-const void* block_kernel(int kind) {
-    if (kind <= 0) return (const void*)k_block_jobs;
-    const int l = (kind - 1) / 3, ri = (kind - 1) % 3;
-    switch (l) {
-        case 0: return block_regs_kernel<1, 8>(ri);
-        case 1: return block_regs_kernel<2, 8>(ri);
-        case 2: return block_regs_kernel<4, 8>(ri);
-        case 3: return block_regs_kernel<8, 8>(ri);
-        case 4: return block_regs_kernel<1, 16>(ri);
-        case 5: return block_regs_kernel<2, 16>(ri);
-        default: return block_regs_kernel<4, 16>(ri);
-    }
-}
-}  // namespace
-
-int refine_block_lds_budget() {
-    static int budget = -1;
-    if (budget < 0) {
-        int dev = 0, maxsh = 65536;
-        if (hipGetDevice(&dev) == hipSuccess)
-            (void)hipDeviceGetAttribute(&maxsh, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-        size_t stat = 0;
-        for (int r = 0; r < kBlockKinds; ++r) {
-            hipFuncAttributes fa;
-            if (hipFuncGetAttributes(&fa, block_kernel(r)) == hipSuccess) stat = std::max(stat, fa.sharedSizeBytes);
-        }
-        long b = std::min<long>(kBlockLdsMax, (long)maxsh - (long)stat - 256);
-        b = std::max<long>(b, 0);
-        for (int r = 0; r < kBlockKinds; ++r) {
-            if (b > 65536 - (long)stat - 256 &&
-                hipFuncSetAttribute(block_kernel(r), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b) != hipSuccess) {
-                (void)hipGetLastError();
-                b = std::max<long>(0, 65536 - (long)stat - 256);
-            }
-        }
-        budget = (int)(b & ~7L);
-    }
-    return budget;
-}
-
-hipError_t launch_block_jobs(const BlockJob* jobs, int njobs, int kind, hipStream_t s) {
-    if (kind < 0 || kind >= kBlockKinds) return hipErrorInvalidValue;
-    const int budget = refine_block_lds_budget();
-    void* args[] = {(void*)&jobs, (void*)&budget};
-    return hipLaunchKernel(block_kernel(kind), dim3(njobs), dim3(kind ? kBlockRegsThreads : kBlockKernelThreads), args,
-                           (size_t)budget, s);
 }
 
 namespace {
