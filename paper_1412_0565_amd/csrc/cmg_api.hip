@@ -107,11 +107,9 @@ int pick_lanes(double avg_deg) {
 // Lanes per row on a level refined inside one workgroup, where a step is
 // one latency chain: G minimises the critical path of the slowest lane
 // group, (rows per group - 1) (avg/G + c) + maxlen/G + c, with c = 8 entry
-// visits standing for the per-row reduction and bookkeeping (threads = 64
-// for the one-wavefront mode of levels up to 256 vertices, else the
-// workgroup).  Meshes get 1-2 lanes; levels with hub rows get more.
-int pick_lanes_block(int n, double avg_deg, int maxlen, int block_threads) {
-    const int threads = n <= 256 ? 64 : block_threads;
+// visits standing for the per-row reduction and bookkeeping.  Meshes get 1-2
+// lanes; levels with hub rows get more.
+int pick_lanes_block(int n, double avg_deg, int maxlen, int threads) {
     const double c = 8.0;
     int best = 1;
     double best_cost = 0.0;
@@ -781,21 +779,8 @@ cmg_status coarsen_chain(cmg_ctx* c, SetupTmp& t, int j0, int* next) {
     job.seed = c->opt.seed;
     job.coarsest_n = c->opt.coarsest_n;
     job.max_levels = max_levels;
-    // scratch: the level-0 setup buffers (n0 >= n and nnz0 >= nnz, and
-    // nnz0 >= n0 since every vertex has a neighbour)
-    job.h = t.h;
-    job.pairseed = t.pairseed;
-    job.rootseed = t.rootseed;
-    job.rank = t.rank;
-    job.members = t.idx;
-    job.astart = (int32_t*)t.k0;  // 2 nnz0 ints
-    job.soff = job.astart + L.n;
-    job.rcount = (int32_t*)t.v1;  // 2 nnz0 ints
+    // scratch: the level-0 setup buffers (nnz0 >= nnz)
     job.mb = (int32_t*)t.k1;
-    job.bcol = t.heads;
-    job.slot = t.slot;
-    job.live = t.live;
-    job.state = t.state;
     job.mw = t.v0;
     ALLOC(job.ai32, int32_t, i32cap);
     job.ai32_cap = i32cap;
@@ -1122,14 +1107,18 @@ int fixed_steps(int k0, double beta, int j, int cap) {
 }
 
 // Single-workgroup levels held as dense matrices: up to 64 vertices always
-// (a step 0.03 us against 0.35 to 0.6 on register rows), up to 128 where
-// rows are short (0.07 against 0.5 to 0.8) or the level has more entries
-// than register rows take without many passes (n = 117, 7000 entries: 4.7
-// us on the CSR arrays).  The levels left between, of a few thousand
-// entries, stay on register rows with their list of long rows (0.9 us).
+// (a step 0.08 us against 0.35 to 0.6 on register rows), up to 128 where
+// rows are short (n = 90: 0.15 against 0.58; at n = 129 to 176 the matrix
+// takes as long as register rows with jumps or longer: n = 159, 1158 steps
+// 0.54 against 0.39 ms), up to 176 where the level is full enough to be
+// read from its CSR arrays otherwise (n = 144, 11076 entries: 0.27 us a
+// step against 2.3 with jumps and 12 without).  The levels left between, of
+// a few thousand entries, stay on register rows with their list of long
+// rows (0.9 us).
 bool dense_block_level(const HostLevel& L) {
-    if (L.n > kDenseBlockN || dense_block_lds(L.n) > refine_block_lds_budget()) return false;
-    return L.n <= 64 || L.nnz <= 16 * (int64_t)L.n || L.nnz > 4096;
+    if (!dense_block_fits(L.n)) return false;
+    const int64_t n = L.n;
+    return n <= 64 || (n <= 128 && L.nnz <= 16 * n) || (L.nnz > 4096 && L.nnz > 32 * n);
 }
 
 cmg_status build_refine_plan(cmg_ctx* c) {
@@ -1184,7 +1173,11 @@ cmg_status build_refine_plan(cmg_ctx* c) {
             L.bregs = p.regs;
             L.bslots = p.slots;
         } else {
-            L.lanes = pick_lanes_block(L.n, L.nnz / (double)std::max(L.n, 1), (int)L.maxlen, kBlockKernelThreads);
+            // a wavefront alone needs no barriers, but leaves the rest of the
+            // CU idle: 144 rows of 77 entries took 12 us a step on one
+            const bool wave = L.n <= 256 && L.nnz <= 1024;
+            L.bwaves = wave ? 1 : kBlockKernelThreads / 64;
+            L.lanes = pick_lanes_block(L.n, L.nnz / (double)std::max(L.n, 1), (int)L.maxlen, 64 * L.bwaves);
         }
     }
     // the dense coarsest solve depends on the hierarchy alone: it is

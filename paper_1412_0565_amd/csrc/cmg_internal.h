@@ -46,11 +46,9 @@ struct ChainJob {
     uint64_t seed;
     int32_t coarsest_n;
     int32_t max_levels;  // levels that may be visited, the first included
-    // scratch (sized for level 0 of the graph)
-    int32_t *h, *pairseed, *rootseed, *rank, *members, *astart, *soff, *rcount, *mb;
-    int32_t* bcol;  // aggregate of each entry's column (nnz0 ints)
-    unsigned long long* slot;
-    uint8_t *live, *state;
+    // scratch of nnz0 entries: coarse rows that outgrow a thread's registers
+    // or wait for their row pointers
+    int32_t* mb;
     double* mw;
     // arenas for the levels produced: agg and row pointers (ai32), columns
     // and weights (acol, aw)
@@ -214,8 +212,8 @@ constexpr int kRegLayoutE[kRegLayouts] = {8, 8, 8, 8, 16, 16, 16};
 // weights; last, levels of at most kDenseBlockN vertices as dense matrices.
 constexpr int kBlockDense = 1 + 2 * 3 * kRegLayouts;
 constexpr int kBlockKinds = kBlockDense + 1;
-constexpr int kDenseBlockN = 128;
-int dense_block_lds(int n);  // LDS bytes such a level needs
+constexpr int kDenseBlockN = 176;
+bool dense_block_fits(int n);  // whether such a level fits the LDS
 hipError_t launch_block_jobs(const BlockJob* jobs, int njobs, int kind, hipStream_t s);
 // Job kernels are specialised by traversal (merge path or G lanes per
 // row) and precision: kind = 2 * t + fp32, t = 0 for the merge path, else

@@ -22,47 +22,41 @@ constexpr uint8_t kSeedC = 1;
 constexpr uint8_t kPartnerC = 2;
 constexpr unsigned long long kNoKeyC = 0xFFFFFFFFFFFFFFFFull;
 
-__device__ __forceinline__ unsigned long long ld_slot(const unsigned long long* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ void st_slot(unsigned long long* p, unsigned long long v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Inclusive scan over a wavefront.
-__device__ __forceinline__ long long wave_scan_incl(long long v) {
+__device__ __forceinline__ int wave_scan_incl(int v) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const long long t = __shfl_up(v, o, kWave);
+        const int t = __shfl_up(v, o, kWave);
         if (lane >= o) v += t;
     }
     return v;
 }
 
-// Exclusive scan of in[0..m) into out[0..m) by the whole workgroup (each
-// thread a contiguous chunk); returns the total.  `in` is read before any
-// out[] element is written, so in == out is allowed.  `sh` holds 17 longs.
-__device__ long long chain_scan(const int32_t* in, int32_t* out, int m, long long* sh) {
+// Exclusive scan of in(0..m-1), out(i, sum before i), by the whole workgroup
+// (each thread a contiguous chunk); returns the total.  A chunk is read
+// again as it is written, so out(i, .) may overwrite what in(i) reads.
+// `sh` holds 17 ints.
+template <class In, class Out>
+__device__ __forceinline__ int chain_scan(int m, int* sh, In in, Out out) {
     const int T = blockDim.x, tid = threadIdx.x;
     const int per = (m + T - 1) / T;
     const int lo = min(m, tid * per), hi = min(m, lo + per);
-    long long s = 0;
-    for (int i = lo; i < hi; ++i) s += in[i];
-    const long long inc = wave_scan_incl(s);
+    int s = 0;
+    for (int i = lo; i < hi; ++i) s += in(i);
+    const int inc = wave_scan_incl(s);
     const int wv = tid >> 6, nw = T >> 6;
     if ((tid & 63) == 63) sh[wv] = inc;
     __syncthreads();
-    long long off = 0, all = 0;
+    int off = 0, all = 0;
     for (int q = 0; q < nw; ++q) {
         if (q < wv) off += sh[q];
         all += sh[q];
     }
-    long long run = off + inc - s;
+    int run = off + inc - s;
     for (int i = lo; i < hi; ++i) {
-        const int x = in[i];
-        out[i] = (int32_t)run;
+        const int x = in(i);
+        out(i, run);
         run += x;
     }
     __syncthreads();
@@ -91,13 +85,68 @@ constexpr int kChainSlots = 12;
 // 3D-grid levels with 27-47 entries per row took 0.27-1.9 ms here against
 // a few hundred microseconds on the grid kernels).
 constexpr int kChainLongRow = 24;
-constexpr size_t kChainLds = sizeof(int32_t) * 2 * (kChainMaxN / 2 + 1);
+
+// Everything per vertex or aggregate lives in LDS (16-bit ids, as a level
+// has at most kChainMaxN = 8192 vertices); only the CSR arrays, the arenas
+// of the levels produced and the rows that outgrow the register slots are
+// in memory.  A phase is a handful of dependent accesses per thread, so its
+// time is their latency: one workgroup on arrays in memory took 177 us for
+// the four levels below 992 vertices and 459 us for the five below 6016.
+// The 8-byte slots of the greedy rounds are dead once the matching stands,
+// and their space then holds the arrays of the aggregates.
+struct ChainLds {
+    union {
+        unsigned long long slot[kChainMaxN];
+        struct {
+            uint16_t rank[kChainMaxN];          // aggregate opened by a vertex
+            uint16_t agg[kChainMaxN];
+            int32_t astart[kChainMaxN / 2 + 1];  // first member of each aggregate
+            int32_t acnt[kChainMaxN / 2];
+        } a;
+    } u;
+    union {
+        uint16_t h[kChainMaxN];
+        uint16_t members[kChainMaxN];
+    } v;
+    union {
+        uint16_t pair[kChainMaxN];
+        int32_t afill[kChainMaxN / 2];
+    } p;
+    union {
+        uint16_t root[kChainMaxN];
+        int32_t soff[kChainMaxN / 2];  // scratch offset of a coarse row
+    } r;
+    union {
+        struct {
+            uint8_t live[kChainMaxN], state[kChainMaxN];
+        } f;
+        int32_t rcount[kChainMaxN / 2];
+    } l;
+};
+static_assert(sizeof(ChainLds) <= 140 * 1024, "one workgroup's LDS");
+
+// a thread's walk over entries [a, b): `many` loads in flight, in order
+template <int U, class F>
+__device__ __forceinline__ void chain_walk(const int32_t* col, const double* w, int a, int b, F f) {
+    for (int e = a; e < b; e += U) {
+        int c[U];
+        double x[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int t = min(e + q, b - 1);
+            c[q] = gld(col, t);
+            x[q] = gld(w, t);
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (e + q < b) f(c[q], x[q]);
+    }
+}
 
 __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
-    extern __shared__ int32_t lds_cnt[];  // acnt, afill
-    int32_t* acnt = lds_cnt;
-    int32_t* afill = lds_cnt + (kChainMaxN / 2 + 1);
-    __shared__ long long sh[17];
+    extern __shared__ double lds_raw[];
+    ChainLds& S = *(ChainLds*)lds_raw;
+    __shared__ int sh[17];
     __shared__ double sm[4 * 16];
     __shared__ int s_bad;
     __shared__ int s_iso;
@@ -117,27 +166,25 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
         // ---- row pass: h, g = 2 max d, largest weight, FP32 rounding, longest row
         double m4[4] = {0.0, 0.0, 0.0, 0.0};
         for (int v = tid; v < n; v += T) {
-            const int a = rp[v], b = rp[v + 1];
+            const int a = gld(rp, v), b = gld(rp, v + 1);
             m4[3] = fmax(m4[3], (double)(b - a));
             double bw = -1.0, d = 0.0;
             int bc = 0x7fffffff;
-            for (int e = a; e < b; ++e) {
-                const double x = w[e];
-                const int c = col[e];
+            chain_walk<4>(col, w, a, b, [&](int c, double x) {
                 d += x;
                 m4[2] = fmax(m4[2], fabs(x - (double)(float)x));
                 if (x > bw || (x == bw && c < bc)) {
                     bw = x;
                     bc = c;
                 }
-            }
+            });
             // a vertex with no neighbour (a component that became one
             // aggregate) names itself and stops the chain below
             if (b == a) {
                 bc = v;
                 s_iso = 1;
             }
-            J.h[v] = bc;
+            S.v.h[v] = (uint16_t)bc;
             m4[0] = fmax(m4[0], 2.0 * d);
             m4[1] = fmax(m4[1], bw);
         }
@@ -175,43 +222,43 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
         }
         // ---- HEC: candidates, greedy rounds
         for (int v = tid; v < n; v += T) {
-            J.pairseed[v] = v;
-            J.live[v] = (hec_key(J.seed, level, v) < hec_key(J.seed, level, J.h[v])) ? 1 : 0;
-            J.state[v] = 0;
-            st_slot(&J.slot[v], kNoKeyC);
+            S.p.pair[v] = (uint16_t)v;
+            S.l.f.live[v] = (hec_key(J.seed, level, v) < hec_key(J.seed, level, S.v.h[v])) ? 1 : 0;
+            S.l.f.state[v] = 0;
+            S.u.slot[v] = kNoKeyC;
         }
         __syncthreads();
         int rounds = 0;
         while (true) {
             for (int v = tid; v < n; v += T) {
-                if (!J.live[v]) continue;
+                if (!S.l.f.live[v]) continue;
                 const unsigned long long kv = hec_key(J.seed, level, v);
-                atomicMin(&J.slot[v], kv);
-                atomicMin(&J.slot[J.h[v]], kv);
+                atomicMin(&S.u.slot[v], kv);
+                atomicMin(&S.u.slot[S.v.h[v]], kv);
             }
             __syncthreads();
             for (int v = tid; v < n; v += T) {
-                if (!J.live[v]) continue;
+                if (!S.l.f.live[v]) continue;
                 const unsigned long long kv = hec_key(J.seed, level, v);
-                const int m = J.h[v];
-                if (ld_slot(&J.slot[v]) == kv && ld_slot(&J.slot[m]) == kv) {
-                    J.state[v] = kSeedC;
-                    J.state[m] = kPartnerC;
-                    J.pairseed[v] = v;
-                    J.pairseed[m] = v;
-                    J.live[v] = 0;
+                const int m = S.v.h[v];
+                if (S.u.slot[v] == kv && S.u.slot[m] == kv) {
+                    S.l.f.state[v] = kSeedC;
+                    S.l.f.state[m] = kPartnerC;
+                    S.p.pair[v] = (uint16_t)v;
+                    S.p.pair[m] = (uint16_t)v;
+                    S.l.f.live[v] = 0;
                 }
             }
             __syncthreads();
             int alive = 0;
             for (int v = tid; v < n; v += T) {
-                if (!J.live[v]) continue;
-                const int m = J.h[v];
-                if (J.state[v] != 0 || J.state[m] != 0) {
-                    J.live[v] = 0;
+                if (!S.l.f.live[v]) continue;
+                const int m = S.v.h[v];
+                if (S.l.f.state[v] != 0 || S.l.f.state[m] != 0) {
+                    S.l.f.live[v] = 0;
                 } else {
-                    st_slot(&J.slot[v], kNoKeyC);
-                    st_slot(&J.slot[m], kNoKeyC);
+                    S.u.slot[v] = kNoKeyC;
+                    S.u.slot[m] = kNoKeyC;
                     alive = 1;
                 }
             }
@@ -219,15 +266,17 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
             if (!__syncthreads_or(alive)) break;
         }
         hd.rounds = rounds;
-        // ---- attach: follow h to a matched vertex; seeds flagged
+        // ---- attach: follow h to a matched vertex
         for (int v = tid; v < n; v += T) {
             int r = v;
-            for (int guard = 0; guard < n && J.state[r] == 0; ++guard) r = J.h[r];
-            J.rootseed[v] = J.pairseed[r];
-            J.rank[v] = (J.state[v] == kSeedC) ? 1 : 0;
+            for (int guard = 0; guard < n && S.l.f.state[r] == 0; ++guard) r = S.v.h[r];
+            S.r.root[v] = S.p.pair[r];
         }
         __syncthreads();
-        const int nc = (int)chain_scan(J.rank, J.rank, n, sh);
+        // number the opening vertices (the slots are dead from here on)
+        const int nc = chain_scan(
+            n, sh, [&](int v) { return S.l.f.state[v] == kSeedC ? 1 : 0; },
+            [&](int v, int q) { S.u.a.rank[v] = (uint16_t)q; });
         if (nc < 2) {
             collapsed = 1;
             stop_reason = 2;
@@ -245,29 +294,32 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
         }
         int32_t* agg = J.ai32 + i32_used;
         hd.agg_off = i32_used;
-        for (int v = tid; v < n; v += T) agg[v] = J.rank[J.rootseed[v]];
         for (int a = tid; a < nc; a += T) {
-            acnt[a] = 0;
-            afill[a] = 0;
+            S.u.a.acnt[a] = 0;
+            S.p.afill[a] = 0;
         }
         if (tid == 0) s_bad = 0;
         __syncthreads();
         // ---- members of each aggregate, in increasing vertex index
-        for (int v = tid; v < n; v += T) atomicAdd(&acnt[agg[v]], 1);
-        __syncthreads();
-        for (int a = tid; a < nc; a += T) J.astart[a] = acnt[a];
-        __syncthreads();
-        chain_scan(J.astart, J.astart, nc, sh);
         for (int v = tid; v < n; v += T) {
-            const int a = agg[v];
-            J.members[J.astart[a] + atomicAdd(&afill[a], 1)] = v;
+            const int a = S.u.a.rank[S.r.root[v]];
+            S.u.a.agg[v] = (uint16_t)a;
+            gst(agg, v, (int32_t)a);
+            atomicAdd(&S.u.a.acnt[a], 1);
+        }
+        __syncthreads();
+        chain_scan(
+            nc, sh, [&](int a) { return S.u.a.acnt[a]; }, [&](int a, int q) { S.u.a.astart[a] = q; });
+        for (int v = tid; v < n; v += T) {
+            const int a = S.u.a.agg[v];
+            S.v.members[S.u.a.astart[a] + atomicAdd(&S.p.afill[a], 1)] = (uint16_t)v;
         }
         __syncthreads();
         for (int a = tid; a < nc; a += T) {
-            int32_t* ms = J.members + J.astart[a];
-            const int cnt = acnt[a];
+            uint16_t* ms = S.v.members + S.u.a.astart[a];
+            const int cnt = S.u.a.acnt[a];
             for (int i = 1; i < cnt; ++i) {
-                const int x = ms[i];
+                const uint16_t x = ms[i];
                 int j = i - 1;
                 while (j >= 0 && ms[j] > x) {
                     ms[j + 1] = ms[j];
@@ -276,9 +328,9 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
                 ms[j + 1] = x;
             }
             int64_t deg = 0;
-            for (int i = 0; i < cnt; ++i) deg += rp[ms[i] + 1] - rp[ms[i]];
+            for (int i = 0; i < cnt; ++i) deg += gld(rp, (int)ms[i] + 1) - gld(rp, (int)ms[i]);
             if (deg > kChainMaxRow) s_bad = 1;
-            J.soff[a] = (int32_t)deg;
+            S.l.rcount[a] = (int32_t)deg;
         }
         __syncthreads();
         if (s_bad) {
@@ -289,140 +341,145 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
             if (tid == 0) J.hdr[k] = hd;
             break;
         }
-        chain_scan(J.soff, J.soff, nc, sh);
-        // aggregate of every entry's column, all threads over all entries:
-        // the row loop below then reads its entries without a dependent load
-        for (int64_t e = tid; e < nnz; e += T) J.bcol[e] = agg[col[e]];
-        __syncthreads();
+        chain_scan(
+            nc, sh, [&](int a) { return S.l.rcount[a]; }, [&](int a, int q) { S.r.soff[a] = q; });
+        int32_t* rpc = J.ai32 + i32_used + n;
+        int32_t* colc = J.acol + cw_used;
+        double* wc = J.aw + cw_used;
         // ---- Galerkin: one thread per coarse row, contributions added in
         // fine CSR order, row sorted by coarse column.  The row is formed in
         // the thread's register slots; a row with more distinct columns
-        // moves to its global scratch and goes on there.
+        // moves to its global scratch and goes on there.  Where every row
+        // has a thread of its own it stays in the registers until the
+        // row lengths are scanned; else it waits in the scratch.
+        const bool once = nc <= T;
+        int rb[kChainSlots];
+        double rw[kChainSlots];
+        int len = 0;
+        bool in_regs = true;
         for (int a = tid; a < nc; a += T) {
-            const int32_t* ms = J.members + J.astart[a];
-            const int cnt = acnt[a];
-            int32_t* mb = J.mb + J.soff[a];
-            double* mw = J.mw + J.soff[a];
+            const uint16_t* ms = S.v.members + S.u.a.astart[a];
+            const int cnt = S.u.a.acnt[a];
+            int32_t* mb = J.mb + S.r.soff[a];
+            double* mw = J.mw + S.r.soff[a];
             // the row in registers: columns rb[0..len) (unused: INT_MAX) and
             // their sums; every slot operation is unrolled and branch-free
-            int rb[kChainSlots];
-            double rw[kChainSlots];
 #pragma unroll
             for (int q = 0; q < kChainSlots; ++q) {
                 rb[q] = 0x7fffffff;
                 rw[q] = 0.0;
             }
-            int len = 0;
-            bool in_regs = true;
+            len = 0;
+            in_regs = true;
             for (int i = 0; i < cnt; ++i) {
                 const int m = ms[i];
-                const int e0 = rp[m], e1 = rp[m + 1];
-                if (e0 >= e1) continue;
-                // one entry ahead: the next entry's coarse column and weight
-                // are loaded before this one is added
-                int bn = J.bcol[e0];
-                double xn = w[e0];
-                for (int e = e0; e < e1; ++e) {
-                    const int b = bn;
-                    const double x = xn;
-                    if (e + 1 < e1) {
-                        xn = w[e + 1];
-                        bn = J.bcol[e + 1];
-                    }
-                    if (b == a) continue;
-                    if (in_regs) {
-                        bool found = false;
+                chain_walk<4>(col, w, gld(rp, m), gld(rp, m + 1), [&](int c, double x) {
+                    const int b = S.u.a.agg[c];
+                    bool found = b == a;  // inside the aggregate: dropped
 #pragma unroll
-                        for (int q = 0; q < kChainSlots; ++q) {
-                            if (rb[q] == b) {
-                                rw[q] += x;
-                                found = true;
-                            }
-                        }
-                        if (found) continue;
-                        if (len < kChainSlots) {
-#pragma unroll
-                            for (int q = 0; q < kChainSlots; ++q) {
-                                if (q == len) {
-                                    rb[q] = b;
-                                    rw[q] = x;
-                                }
-                            }
-                            ++len;
-                            continue;
-                        }
-                        // more columns than slots: the row goes on in global scratch
-#pragma unroll
-                        for (int q = 0; q < kChainSlots; ++q) {
-                            mb[q] = rb[q];
-                            mw[q] = rw[q];
-                        }
-                        in_regs = false;
+                    for (int q = 0; q < kChainSlots; ++q) {
+                        const bool here = rb[q] == b;
+                        rw[q] = here ? rw[q] + x : rw[q];
+                        found = found || here;
                     }
-                    int q = 0;
-                    while (q < len && mb[q] != b) ++q;
-                    if (q == len) {
-                        mb[len] = b;
-                        mw[len] = x;
-                        ++len;
-                    } else {
-                        mw[q] += x;
+#pragma unroll
+                    for (int q = 0; q < kChainSlots; ++q) {
+                        const bool here = !found && q == len;
+                        rb[q] = here ? b : rb[q];
+                        rw[q] = here ? x : rw[q];
                     }
-                }
+                    len += found ? 0 : 1;
+                });
             }
-            if (in_regs) {
+            if (len <= kChainSlots) {
                 // odd-even transposition sort by column (unused slots last)
 #pragma unroll
                 for (int pass = 0; pass < kChainSlots; ++pass) {
 #pragma unroll
                     for (int q = pass & 1; q + 1 < kChainSlots; q += 2) {
-                        if (rb[q] > rb[q + 1]) {
-                            const int tb = rb[q];
-                            rb[q] = rb[q + 1];
-                            rb[q + 1] = tb;
-                            const double tw = rw[q];
-                            rw[q] = rw[q + 1];
-                            rw[q + 1] = tw;
+                        const bool swap = rb[q] > rb[q + 1];
+                        const int tb = rb[q];
+                        const double tw = rw[q];
+                        rb[q] = swap ? rb[q + 1] : tb;
+                        rb[q + 1] = swap ? tb : rb[q + 1];
+                        rw[q] = swap ? rw[q + 1] : tw;
+                        rw[q + 1] = swap ? tw : rw[q + 1];
+                    }
+                }
+                if (!once) {
+#pragma unroll
+                    for (int q = 0; q < kChainSlots; ++q) {
+                        if (q < len) {
+                            gst(mb, q, (int32_t)rb[q]);
+                            gst(mw, q, rw[q]);
                         }
                     }
                 }
+            } else {
+                // more columns than slots: the row is formed again from its
+                // first entry, in the scratch
+                in_regs = false;
+                len = 0;
+                for (int i = 0; i < cnt; ++i) {
+                    const int m = ms[i];
+                    const int e1 = gld(rp, m + 1);
+                    for (int e = gld(rp, m); e < e1; ++e) {
+                        const int b = S.u.a.agg[gld(col, e)];
+                        const double x = gld(w, e);
+                        if (b == a) continue;
+                        int q = 0;
+                        while (q < len && mb[q] != b) ++q;
+                        if (q == len) {
+                            mb[len] = b;
+                            mw[len] = x;
+                            ++len;
+                        } else {
+                            mw[q] += x;
+                        }
+                    }
+                }
+                for (int i = 1; i < len; ++i) {
+                    const int b = mb[i];
+                    const double x = mw[i];
+                    int j = i - 1;
+                    while (j >= 0 && mb[j] > b) {
+                        mb[j + 1] = mb[j];
+                        mw[j + 1] = mw[j];
+                        --j;
+                    }
+                    mb[j + 1] = b;
+                    mw[j + 1] = x;
+                }
+            }
+            S.l.rcount[a] = len;
+        }
+        __syncthreads();
+        // row pointers, in memory and in place of the lengths' scratch use
+        const int64_t nnzc = chain_scan(
+            nc, sh, [&](int a) { return S.l.rcount[a]; },
+            [&](int a, int q) {
+                gst(rpc, a, (int32_t)q);
+                S.p.afill[a] = q;
+            });
+        if (tid == 0) rpc[nc] = (int32_t)nnzc;
+        for (int a = tid; a < nc; a += T) {
+            const int base = S.p.afill[a];
+            if (once && in_regs) {
 #pragma unroll
                 for (int q = 0; q < kChainSlots; ++q) {
                     if (q < len) {
-                        mb[q] = rb[q];
-                        mw[q] = rw[q];
+                        gst(colc, base + q, (int32_t)rb[q]);
+                        gst(wc, base + q, rw[q]);
                     }
                 }
-                J.rcount[a] = len;
                 continue;
             }
-            for (int i = 1; i < len; ++i) {
-                const int b = mb[i];
-                const double x = mw[i];
-                int j = i - 1;
-                while (j >= 0 && mb[j] > b) {
-                    mb[j + 1] = mb[j];
-                    mw[j + 1] = mw[j];
-                    --j;
-                }
-                mb[j + 1] = b;
-                mw[j + 1] = x;
-            }
-            J.rcount[a] = len;
-        }
-        __syncthreads();
-        int32_t* rpc = J.ai32 + i32_used + n;
-        const int64_t nnzc = chain_scan(J.rcount, rpc, nc, sh);
-        if (tid == 0) rpc[nc] = (int32_t)nnzc;
-        int32_t* colc = J.acol + cw_used;
-        double* wc = J.aw + cw_used;
-        for (int a = tid; a < nc; a += T) {
-            const int32_t* mb = J.mb + J.soff[a];
-            const double* mw = J.mw + J.soff[a];
-            const int base = rpc[a], len = J.rcount[a];
-            for (int q = 0; q < len; ++q) {
-                colc[base + q] = mb[q];
-                wc[base + q] = mw[q];
+            const int32_t* mb = J.mb + S.r.soff[a];
+            const double* mw = J.mw + S.r.soff[a];
+            const int l = S.l.rcount[a];
+            for (int q = 0; q < l; ++q) {
+                gst(colc, base + q, gld(mb, q));
+                gst(wc, base + q, gld(mw, q));
             }
         }
         if (tid == 0) J.hdr[k] = hd;
@@ -447,7 +504,12 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
 }  // namespace
 
 hipError_t launch_coarsen_chain(const ChainJob& job, hipStream_t s) {
-    hipLaunchKernelGGL(k_coarsen_chain, dim3(1), dim3(kChainThreads), kChainLds, s, job);
+    if (job.n0 > kChainMaxN) return hipErrorInvalidValue;
+    // more than 64 KiB of LDS for one workgroup has to be asked for
+    static const hipError_t asked = hipFuncSetAttribute(
+        (const void*)k_coarsen_chain, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(ChainLds));
+    if (asked != hipSuccess) return asked;
+    hipLaunchKernelGGL(k_coarsen_chain, dim3(1), dim3(kChainThreads), sizeof(ChainLds), s, job);
     return hipGetLastError();
 }
 

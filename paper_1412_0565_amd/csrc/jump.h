@@ -46,6 +46,8 @@ constexpr int kJumpPlain = 24;  // a multiple of 8
 constexpr double kJumpMargin = 1.02;
 // 1 - (u, v) from the moments carries about 1e-13 of absolute error.
 constexpr double kJumpTolMin = 1e-10;
+// Steps to try where 1 - (u, v) rises.
+constexpr double kJumpRising = 512.0;
 // ||(B/g)^K v|| may fall to e^-3 within a jump (its error is relative to ||v||).
 constexpr double kJumpDecay = 3.0;
 
@@ -74,8 +76,11 @@ __device__ __forceinline__ int jump_plan(double utv, double utvp, double tol, do
     double want = (double)left;
     if (tol >= 0.0) {
         const double dl = 1.0 - utv, dp = 1.0 - utvp;
-        if (!(dl < dp) || !(dl > tol)) return 0;
-        want = 0.9 * (log(dl / tol) / log(dp / dl)) - 8.0;
+        if (!(dl > tol)) return 0;
+        // a level whose 1 - (u, v) rises (the vector turns from one mode to
+        // a slower one) is far from its end: a power-law level of 594
+        // vertices rose for 1310 of its 2781 steps
+        want = dl < dp ? 0.9 * (log(dl / tol) / log(dp / dl)) - 8.0 : kJumpRising;
     }
     return jump_steps(want, r, left);
 }
@@ -155,7 +160,7 @@ __device__ __forceinline__ void jump_judge(const double* dl, int ns, int K, doub
     *safe = 2 * K;
     const int s1 = ns - 1, s0 = ns - 1 - ns / 16;
     const double d0 = dl[s0], d1 = dl[s1];
-    double more = (double)kJumpMaxK;
+    double more = d1 < d0 ? (double)kJumpMaxK : 2.0 * (double)K;
     if (d1 < d0 && d1 > tol)
         more = 0.9 * (log(d1 / tol) / log(d0 / d1)) * (double)(jump_sample(s1, ns, K) - jump_sample(s0, ns, K));
     *next = K + (int)fmin(more, (double)kJumpMaxK);

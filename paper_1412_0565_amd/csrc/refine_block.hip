@@ -29,12 +29,13 @@ __device__ __forceinline__ void stx(T* p, int i, T v) {
 }
 
 // Bytes of the LDS image of a level: two vectors, weights (FP32 when that
-// is exact), row pointers, columns (uint16 when n <= 65536).
-__device__ __forceinline__ size_t staged_bytes(const LevelDev& L, int w32, int col16) {
+// is exact), row pointers, columns (uint16: an image that fits has fewer
+// than 65536 rows).
+__device__ __forceinline__ size_t staged_bytes(const LevelDev& L, int w32) {
     size_t b = align8(16 * (size_t)L.n);
     b += align8((size_t)L.nnz * (w32 ? 4 : 8));
     b += align8(4 * ((size_t)L.n + 1));
-    b += align8((size_t)L.nnz * (col16 ? 2 : 4));
+    b += align8((size_t)L.nnz * 2);
     return b;
 }
 
@@ -131,18 +132,17 @@ __device__ __forceinline__ void step_sum4(double (&v)[4], double* red, int& pari
     }
 }
 
-// A product of a jump on a single-workgroup level, as in JumpOp.
+// A product of a jump on a single-workgroup level, as in JumpOp (the jump's
+// sum is added up from the products' vectors by their own pass).
 struct SmallJump {
     bool first;
-    double be, cj;
-    double* jsum;
-    double* jback;
+    double be;
 };
 
 // One PI step (JUMP: one product of a jump) of a small level, rows shared by
 // `nthr` threads in G-lane groups.  Pointers are either all LDS (staged
 // modes) or all global.
-template <int G, bool W32, bool C16, bool LDS, bool JUMP>
+template <int G, bool W32, bool LDS, bool JUMP>
 __device__ __forceinline__ void pi_small(int n, int nthr, const int32_t* rp, const void* colp,
                                          const void* wp, double g, const double* win, double* wout,
                                          double mu, double s, const SmallJump& sj, double (&acc)[4]) {
@@ -151,12 +151,9 @@ __device__ __forceinline__ void pi_small(int n, int nthr, const int32_t* rp, con
     for (int i = (int)(threadIdx.x / G); i < n; i += ngroups) {
         const int a = ldx<LDS>(rp, i), b = ldx<LDS>(rp, i + 1);
         const double wi = ldx<LDS>(win, i);
-        double sum = wi, z = 0.0;
+        double z = 0.0;
         if constexpr (JUMP) {
-            if (!sj.first && lane == 0) {
-                sum = gld(sj.jsum, i);
-                z = ldx<LDS>(wout, i);
-            }
+            if (!sj.first) z = ldx<LDS>(wout, i);
         }
         double t = 0.0;
         int e = a + lane;
@@ -168,7 +165,7 @@ __device__ __forceinline__ void pi_small(int n, int nthr, const int32_t* rp, con
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int f = e + q * G;
-                if constexpr (C16) c[q] = (int)ldx<LDS>((const uint16_t*)colp, f);
+                if constexpr (LDS) c[q] = (int)ldx<LDS>((const uint16_t*)colp, f);
                 else c[q] = ldx<LDS>((const int32_t*)colp, f);
                 if constexpr (W32) wt[q] = (double)ldx<LDS>((const float*)wp, f);
                 else wt[q] = ldx<LDS>((const double*)wp, f);
@@ -181,7 +178,7 @@ __device__ __forceinline__ void pi_small(int n, int nthr, const int32_t* rp, con
         for (; e < b; e += G) {
             int c;
             double wt;
-            if constexpr (C16) c = (int)ldx<LDS>((const uint16_t*)colp, e);
+            if constexpr (LDS) c = (int)ldx<LDS>((const uint16_t*)colp, e);
             else c = ldx<LDS>((const int32_t*)colp, e);
             if constexpr (W32) wt = (double)ldx<LDS>((const float*)wp, e);
             else wt = ldx<LDS>((const double*)wp, e);
@@ -192,8 +189,6 @@ __device__ __forceinline__ void pi_small(int n, int nthr, const int32_t* rp, con
             if constexpr (JUMP) {
                 const double y = (sj.first ? wi : 2.0 * wi) + sj.be * t - z;
                 stx<LDS>(wout, i, y);
-                gst(sj.jsum, i, sum + sj.cj * y);
-                if (sj.first) gst(sj.jback, i, wi);
                 acc[0] += wi * y;
                 acc[1] += y * y;
                 acc[2] += wi * wi;
@@ -211,20 +206,22 @@ __device__ __forceinline__ void pi_small(int n, int nthr, const int32_t* rp, con
 }
 
 // the same for a run-time G
-template <bool W32, bool C16, bool LDS, bool JUMP>
+template <bool W32, bool LDS, bool JUMP>
 __device__ __forceinline__ void pi_small_any(int G, int n, int nthr, const int32_t* rp, const void* colp,
                                              const void* wp, double g, const double* win, double* wout, double mu,
                                              double s, const SmallJump& sj, double (&acc)[4]) {
     switch (G) {
-        case 1: pi_small<1, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-        case 2: pi_small<2, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-        case 4: pi_small<4, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-        case 8: pi_small<8, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-        case 16: pi_small<16, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-        case 32: pi_small<32, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
-        default: pi_small<64, W32, C16, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        case 1: pi_small<1, W32, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        case 2: pi_small<2, W32, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        case 4: pi_small<4, W32, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        case 8: pi_small<8, W32, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        case 16: pi_small<16, W32, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        case 32: pi_small<32, W32, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
+        default: pi_small<64, W32, LDS, JUMP>(n, nthr, rp, colp, wp, g, win, wout, mu, s, sj, acc); break;
     }
 }
+
+constexpr int kJumpSums = 4;  // entries of a jump's sum that a thread keeps in registers
 
 // Moments and samples of a jump, and its verdict.
 struct JumpLds {
@@ -512,7 +509,7 @@ struct RegRows {
 // Prolongation, deflation, normalisation and PI steps of one small level
 // read from its CSR arrays.  MODE 0: LDS image, one wavefront; 1: LDS
 // image, whole workgroup; 2: global memory, whole workgroup.
-template <int MODE, bool W32, bool C16>
+template <int MODE, bool W32>
 __device__ void small_level(const LevelDev& L, const SmallIn& in, double* lds, double* red, int& parity,
                             int* stop_flag, JumpLds* js, int nw_run, LevelState& out) {
     constexpr bool WAVE = (MODE == 0);
@@ -580,7 +577,7 @@ __device__ void small_level(const LevelDev& L, const SmallIn& in, double* lds, d
             const double* win = cur ? b1 : b0;
             double* wout = cur ? b0 : b1;
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            pi_small_any<W32, C16, LDS, false>(L.lanes, n, nact, rp, colp, wp, L.g, win, wout, mu, s, SmallJump{}, acc);
+            pi_small_any<W32, LDS, false>(L.lanes, n, nact, rp, colp, wp, L.g, win, wout, mu, s, SmallJump{}, acc);
             step_sum4<WAVE>(acc, red, parity, nw);
             ++bar;
             const double mu2 = acc[0] / (double)n;
@@ -610,25 +607,57 @@ __device__ void small_level(const LevelDev& L, const SmallIn& in, double* lds, d
             while (K > 0) {
                 const int d = jump_products(K);
                 SmallJump sj;
-                sj.jsum = L.jsum;
-                sj.jback = L.jback;
-                sj.cj = 2.0 * (double)K / (double)(K + 1);
+                double cj = 2.0 * (double)K / (double)(K + 1);
+                // the jump's sum: up to kJumpSums entries per thread in
+                // registers, else in memory
+                const bool regs = n <= kJumpSums * nact;
+                double sums[kJumpSums];
+                const double* src = cur ? b1 : b0;
+#pragma unroll
+                for (int q = 0; q < kJumpSums; ++q) {
+                    const int i = (int)threadIdx.x + q * nact;
+                    sums[q] = regs && i < n ? ldx<LDS>(src, i) : 0.0;
+                }
+                for (int i = threadIdx.x; i < n; i += nact) {
+                    const double x = ldx<LDS>(src, i);
+                    gst(L.jback, i, x);
+                    if (!regs) gst(L.jsum, i, x);
+                }
                 for (int j = 0; j < d; ++j) {
                     sj.first = j == 0;
                     sj.be = (j == 0 ? 2.0 : 4.0) / L.g;
                     double sum4[4] = {0.0, 0.0, 0.0, 0.0};
-                    pi_small_any<W32, C16, LDS, true>(L.lanes, n, nact, rp, colp, wp, L.g, cur ? b1 : b0,
-                                                      cur ? b0 : b1, mu, s, sj, sum4);
+                    double* dst = cur ? b0 : b1;
+                    pi_small_any<W32, LDS, true>(L.lanes, n, nact, rp, colp, wp, L.g, cur ? b1 : b0, dst, mu, s, sj,
+                                                 sum4);
                     step_sum4<WAVE>(sum4, red, parity, nw);
                     small_bar<WAVE>(stop_flag, bar);
                     if (threadIdx.x == 0) jump_moments(js->mom, j, sum4[0], sum4[1], sum4[2]);
-                    sj.cj = jump_coef(sj.cj, K, j + 1);
+                    if (regs) {
+#pragma unroll
+                        for (int q = 0; q < kJumpSums; ++q) {
+                            const int i = (int)threadIdx.x + q * nact;
+                            if (i < n) sums[q] += cj * ldx<LDS>((const double*)dst, i);
+                        }
+                    } else {
+                        for (int i = threadIdx.x; i < n; i += nact)
+                            gst(L.jsum, i, gld(L.jsum, i) + cj * ldx<LDS>((const double*)dst, i));
+                    }
+                    cj = jump_coef(cj, K, j + 1);
                     cur ^= 1;
                 }
                 int more = 0;
                 const bool keep = small_jump_end<WAVE>(K, d, in.tol, js, red, parity, stop_flag, bar, nw, &more, &hold);
-                const double* src = keep ? L.jsum : L.jback;
-                for (int i = threadIdx.x; i < n; i += nact) stx<LDS>(b0, i, gld(src, i));
+                if (regs && keep) {
+#pragma unroll
+                    for (int q = 0; q < kJumpSums; ++q) {
+                        const int i = (int)threadIdx.x + q * nact;
+                        if (i < n) stx<LDS>(b0, i, sums[q]);
+                    }
+                } else {
+                    const double* from = keep ? L.jsum : L.jback;
+                    for (int i = threadIdx.x; i < n; i += nact) stx<LDS>(b0, i, gld(from, i));
+                }
                 if (keep) {
                     k += K;
                     small_normalise<WAVE, LDS>(n, nact, b0, red, parity, stop_flag, bar, nw, mu, s);
@@ -682,10 +711,10 @@ __device__ void small_level(const LevelDev& L, const SmallIn& in, double* lds, d
 // prolongation, deflation, normalisation and every PI step separated only
 // by workgroup (or wavefront) barriers, so thousands of steps cost no
 // launches.  A level whose CSR and two vectors fit in `lds_budget` bytes
-// is first copied to LDS (columns as uint16 when n <= 65536, weights as
+// is first copied to LDS (columns as uint16, weights as
 // FP32 when that is exact) and its steps touch no global memory; levels of
-// at most kWaveRows vertices then run on a single wavefront, larger ones on
-// LevelDev::bwaves wavefronts (0: all).  Larger levels stream from global
+// LevelDev::bwaves = 1 then run on a single wavefront, the others on that
+// many (0: one up to kWaveRows vertices, else all).  Larger levels stream from global
 // memory (L2).  The final vector of each level goes to buf0 (its
 // predecessor to buf1).
 __global__ void __launch_bounds__(kBlockKernelThreads)
@@ -712,13 +741,8 @@ __global__ void __launch_bounds__(kBlockKernelThreads)
         const int n = L.n;
         const int nwmax = (int)(blockDim.x >> 6);
         const int nw = L.bwaves > 0 ? min(L.bwaves, nwmax) : (n <= kWaveRows ? 1 : nwmax);
-        const int c16 = (n <= 65536) ? 1 : 0;
-        int w32 = 0;
-        size_t need = staged_bytes(L, 0, c16);
-        if (need > (size_t)lds_budget && L.w32exact) {
-            w32 = 1;
-            need = staged_bytes(L, 1, c16);
-        }
+        const int w32 = L.w32exact ? 1 : 0;
+        const size_t need = staged_bytes(L, w32);
         const bool staged = need <= (size_t)lds_budget;
         const int mode = staged ? (nw == 1 ? 0 : 1) : 2;
         if (staged) {
@@ -732,8 +756,7 @@ __global__ void __launch_bounds__(kBlockKernelThreads)
             for (int e = threadIdx.x; e < (int)L.nnz; e += blockDim.x) {
                 const int cv = gld(L.col, e);
                 const double wv = gld(L.w64, e);
-                if (c16) sst((uint16_t*)cdst, e, (uint16_t)cv);
-                else sst((int32_t*)cdst, e, (int32_t)cv);
+                sst((uint16_t*)cdst, e, (uint16_t)cv);
                 if (w32) sst((float*)wdst, e, (float)wv);
                 else sst((double*)wdst, e, wv);
             }
@@ -757,24 +780,14 @@ __global__ void __launch_bounds__(kBlockKernelThreads)
         LevelState o;
         if (mode == 0) {
             if (threadIdx.x < 64) {
-                if (w32) {
-                    if (c16) small_level<0, true, true>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
-                    else small_level<0, true, false>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
-                } else {
-                    if (c16) small_level<0, false, true>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
-                    else small_level<0, false, false>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
-                }
+                if (w32) small_level<0, true>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
+                else small_level<0, false>(L, in, lds, red, parity, s_stop, &s_jump, 1, o);
             }
         } else if (mode == 1) {
-            if (w32) {
-                if (c16) small_level<1, true, true>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
-                else small_level<1, true, false>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
-            } else {
-                if (c16) small_level<1, false, true>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
-                else small_level<1, false, false>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
-            }
+            if (w32) small_level<1, true>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
+            else small_level<1, false>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
         } else {
-            small_level<2, false, false>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
+            small_level<2, false>(L, in, lds, red, parity, s_stop, &s_jump, nw, o);
         }
         if (threadIdx.x == 0) {
             o.ticks = wall_clock64() - t_start;
@@ -1084,27 +1097,47 @@ __global__ void __launch_bounds__(kBlockRegsThreads)
 // Per step that is n/4 matrix-instruction latencies (64 cycles) and two
 // barriers over 16, against a chain of gathers, sums over the workgroup and
 // a square root: 0.35 to 0.8 us a step before.
+//
+// The powers are symmetric, so only the 16 x 16 tiles on and below the
+// diagonal are kept and formed (half the products, and 11 tiles a side fit
+// the LDS); the entries of a tile are swizzled so that its rows and its
+// columns are both read without bank conflicts.
 typedef double v4d __attribute__((ext_vector_type(4)));
+
+template <int NT>
+struct DenseTiles {
+    double* p;
+    // entry (r, c) of tile (i, j)
+    __device__ __forceinline__ static int at(int i, int j, int r, int c) {
+        return i >= j ? ((i * (i + 1)) / 2 + j) * 256 + r * 16 + (c ^ r) : ((j * (j + 1)) / 2 + i) * 256 + c * 16 + (r ^ c);
+    }
+    __device__ __forceinline__ double get(int i, int j, int r, int c) const { return sld(p, at(i, j, r, c)); }
+    __device__ __forceinline__ void put(int i, int j, int r, int c, double v) { sst(p, at(i, j, r, c), v); }
+};
 
 template <int NT>
 __device__ void dense_level(const LevelDev& L, const SmallIn& in, double* lds, double* red, double* part,
                             LevelState& out) {
-    constexpr int N = 16 * NT;      // rows, padded with zeros
-    double* Am = lds;               // N x N, columns swizzled by row
-    double* X0 = lds + N * N;       // N x 16
-    double* X1 = lds;               // N x 16, over the matrix once that is in registers
-    // the sixteen rows of a fragment start in different banks
-    auto at = [](int r, int c) { return r * N + (c ^ (r & 15)); };
+    constexpr int N = 16 * NT;                    // rows, padded with zeros
+    constexpr int NTILE = NT * (NT + 1) / 2;
+    constexpr int RT = NT > 8 ? 2 : 1;            // row tiles of a wavefront
+    constexpr int CW = NT <= 4 ? 4 : NT < 8 ? 2 : 8;  // wavefronts that check, with no tile of their own if NT < 8
+    constexpr int C0 = NT < 8 ? 8 - CW : 0;       // the first of them
+    constexpr int MAXT = (NTILE + 7) / 8;         // tiles of a wavefront in a squaring
+    DenseTiles<NT> M{lds};
+    double* X0 = lds + NTILE * 256;  // N x 16
+    double* X1 = lds;                // N x 16, over the matrix once that is in registers
     const int n = L.n;
     const int tid = (int)threadIdx.x, T = (int)blockDim.x;
     const int lane = tid & 63, l16 = lane & 15, l4 = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool act = wv < NT;
     // B' and the start vector
     const double inv_n = 1.0 / (double)n, inv_g = 1.0 / L.g;
-    for (int t = tid; t < N * N; t += T) {
-        const int i = t / N, j = t - i * N;
-        sst(Am, at(i, j), i < n && j < n ? -inv_n : 0.0);
+    for (int t = tid; t < NTILE * 256; t += T) {
+        int i = 0;
+        while ((i + 1) * (i + 2) / 2 <= (t >> 8)) ++i;
+        const int j = (t >> 8) - i * (i + 1) / 2, r = (t >> 4) & 15, c = (t & 15) ^ r;
+        sst(lds, t, 16 * i + r < n && 16 * j + c < n ? -inv_n : 0.0);
     }
     for (int t = tid; t < N * 16; t += T) sst(X0, t, 0.0);
     double v = 0.0;
@@ -1121,54 +1154,93 @@ __device__ void dense_level(const LevelDev& L, const SmallIn& in, double* lds, d
     if (tid < n) {
         sst(X0, tid * 16, dv * (1.0 / sqrt(ss[0])));
         double d = 0.0;
-        const int b = gld(L.rp, tid + 1);
-        for (int e = gld(L.rp, tid); e < b; ++e) {
-            const double a = gld(L.w64, e);
-            const int c = at(tid, gld(L.col, e));
-            d += a;
-            sst(Am, c, sld(Am, c) + a * inv_g);
+        const int a = gld(L.rp, tid), b = gld(L.rp, tid + 1);
+        for (int e = a; e < b; e += 4) {
+            int c[4];
+            double w[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                c[q] = gld(L.col, min(e + q, b - 1));
+                w[q] = gld(L.w64, min(e + q, b - 1));
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (e + q >= b) continue;
+                d += w[q];
+                // columns below the diagonal fill the lower triangle (and
+                // both halves of a diagonal tile)
+                if ((c[q] >> 4) > (tid >> 4)) continue;
+                const int t = M.at(tid >> 4, c[q] >> 4, tid & 15, c[q] & 15);
+                sst(lds, t, w[q] * inv_g - inv_n);
+            }
         }
-        sst(Am, at(tid, tid), sld(Am, at(tid, tid)) + (L.g - d) * inv_g);
+        M.put(tid >> 4, tid >> 4, tid & 15, tid & 15, (L.g - d) * inv_g - inv_n);
     }
     __syncthreads();
     // the first sixteen iterates and M = B'^16
-    double af[4 * NT];
-    v4d y = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
-    for (int p = 0; p <= 4; ++p) {
-        if (act) {
+    for (int p = 0; p < 4; ++p) {
+        v4d y[RT];
 #pragma unroll
-            for (int t = 0; t < 4 * NT; ++t) af[t] = sld(Am, at(16 * wv + l16, 4 * t + l4));
+        for (int u = 0; u < RT; ++u) {
+            const int i = wv + 8 * u;
+            y[u] = v4d{0.0, 0.0, 0.0, 0.0};
+            if (i >= NT) continue;
+#pragma unroll 2
+            for (int k = 0; k < NT; ++k) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    y[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                        M.get(i, k, l16, 4 * t + l4), sld(X0, (16 * k + 4 * t + l4) * 16 + l16), y[u], 0, 0, 0);
+            }
         }
-        if (p == 4) break;
-        v4d c[NT];
-        if (act) {
-            y = v4d{0.0, 0.0, 0.0, 0.0};
+        // the square's tiles, dealt out over the wavefronts
+        v4d c[MAXT];
 #pragma unroll
-            for (int t = 0; t < 4 * NT; ++t)
-                y = __builtin_amdgcn_mfma_f64_16x16x4f64(af[t], sld(X0, (4 * t + l4) * 16 + l16), y, 0, 0, 0);
+        for (int q = 0; q < MAXT; ++q) {
+            const int tile = wv + 8 * q;
+            c[q] = v4d{0.0, 0.0, 0.0, 0.0};
+            if (tile >= NTILE) continue;
+            int i = 0;
+            while ((i + 1) * (i + 2) / 2 <= tile) ++i;
+            const int j = tile - i * (i + 1) / 2;
+#pragma unroll 2
+            for (int k = 0; k < NT; ++k) {
 #pragma unroll
-            for (int q = 0; q < NT; ++q) c[q] = v4d{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int t = 0; t < 4 * NT; ++t) {
-#pragma unroll
-                for (int q = 0; q < NT; ++q)
-                    c[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[t], sld(Am, at(4 * t + l4, 16 * q + l16)), c[q], 0, 0, 0);
+                for (int t = 0; t < 4; ++t)
+                    c[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(M.get(i, k, l16, 4 * t + l4),
+                                                                M.get(k, j, 4 * t + l4, l16), c[q], 0, 0, 0);
             }
         }
         __syncthreads();
-        if (act) {
-            const int done = 1 << p;  // columns there are
+        const int done = 1 << p;  // columns there are
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int r = 16 * wv + 4 * q + l4;
-                if (l16 < done) sst(X0, r * 16 + l16 + done, y[q]);
+        for (int u = 0; u < RT; ++u) {
+            const int i = wv + 8 * u;
+            if (i >= NT || l16 >= done) continue;
 #pragma unroll
-                for (int k = 0; k < NT; ++k) sst(Am, at(r, 16 * k + l16), c[k][q]);
+            for (int q = 0; q < 4; ++q) sst(X0, (16 * i + 4 * q + l4) * 16 + l16 + done, y[u][q]);
+        }
+#pragma unroll
+        for (int q = 0; q < MAXT; ++q) {
+            const int tile = wv + 8 * q;
+            if (tile >= NTILE) continue;
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const int r = 4 * h + l4;
+                sst(lds, tile * 256 + r * 16 + (l16 ^ r), c[q][h]);
             }
         }
         __syncthreads();
     }
+    double af[RT][4 * NT];
+#pragma unroll
+    for (int u = 0; u < RT; ++u) {
+        if (wv + 8 * u >= NT) continue;
+#pragma unroll
+        for (int t = 0; t < 4 * NT; ++t) af[u][t] = M.get(wv + 8 * u, t >> 2, l16, 4 * (t & 3) + l4);
+    }
+    __syncthreads();  // the matrix is read before the second block overwrites it
     // blocks of sixteen steps: step 16 b + c is column c of block b
     double* X = X0;
     double* Y = X1;
@@ -1179,27 +1251,36 @@ __device__ void dense_level(const LevelDev& L, const SmallIn& in, double* lds, d
     double utv = 0.0, sc = 1.0, sp = 1.0;
     while (true) {
         // norms of the columns and products with the one before
-        double a2[2] = {0.0, 0.0};
-        if (act) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int r = 16 * wv + 4 * q + l4;
+        if (wv >= C0) {
+            double a0 = 0.0, a1 = 0.0;
+#pragma unroll 4
+            for (int r = 4 * (wv - C0) + l4; r < N; r += 4 * CW) {
                 const double x = sld(X, r * 16 + l16);
                 const double z = l16 > 0 ? sld(X, r * 16 + l16 - 1) : sld(Y, r * 16 + 15);
-                a2[0] += x * x;
-                a2[1] += x * z;
+                a0 += x * x;
+                a1 += x * z;
             }
-            a2[0] = pair_sum_rows<32>(pair_sum_rows<16>(a2[0]));
-            a2[1] = pair_sum_rows<32>(pair_sum_rows<16>(a2[1]));
+            a0 = pair_sum_rows<32>(pair_sum_rows<16>(a0));
+            a1 = pair_sum_rows<32>(pair_sum_rows<16>(a1));
             if (lane < 16) {
-                sst(part, wv * 32 + l16, a2[0]);
-                sst(part, wv * 32 + 16 + l16, a2[1]);
+                sst(part, (wv - C0) * 32 + l16, a0);
+                sst(part, (wv - C0) * 32 + 16 + l16, a1);
             }
+        }
+        // the next block meanwhile
+        v4d y[RT];
+#pragma unroll
+        for (int u = 0; u < RT; ++u) {
+            y[u] = v4d{0.0, 0.0, 0.0, 0.0};
+            if (wv + 8 * u >= NT) continue;
+#pragma unroll
+            for (int t = 0; t < 4 * NT; ++t)
+                y[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[u][t], sld(X, (4 * t + l4) * 16 + l16), y[u], 0, 0, 0);
         }
         __syncthreads();
         double n2 = 0.0, dd = 0.0;
 #pragma unroll
-        for (int q = 0; q < NT; ++q) {
+        for (int q = 0; q < CW; ++q) {
             n2 += sld(part, q * 32 + l16);
             dd += sld(part, q * 32 + 16 + l16);
         }
@@ -1218,20 +1299,15 @@ __device__ void dense_level(const LevelDev& L, const SmallIn& in, double* lds, d
             hit = utv < 1.0 - in.tol ? 1 : 0;
             break;
         }
-        // the next block, scaled by a power of two against underflow
+        // scaled by a power of two against underflow
         const double last = read_lane(n2, 15);
         plast = read_lane(rn, 15);
         const double scale = last < 0x1p-200 ? 0x1p+100 : 1.0;
-        if (act) {
-            y = v4d{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int t = 0; t < 4 * NT; ++t)
-                y = __builtin_amdgcn_mfma_f64_16x16x4f64(af[t], sld(X, (4 * t + l4) * 16 + l16), y, 0, 0, 0);
-        }
-        __syncthreads();
-        if (act) {
+        for (int u = 0; u < RT; ++u) {
+            if (wv + 8 * u >= NT) continue;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) sst(Y, (16 * wv + 4 * q + l4) * 16 + l16, y[q] * scale);
+            for (int q = 0; q < 4; ++q) sst(Y, (16 * (wv + 8 * u) + 4 * q + l4) * 16 + l16, y[u][q] * scale);
         }
         __syncthreads();
         double* const t = X;
@@ -1259,10 +1335,12 @@ __device__ void dense_level(const LevelDev& L, const SmallIn& in, double* lds, d
     out.ticks = 0;
 }
 
-// tiles of the kernel that takes a level of nt tiles
-__host__ __device__ constexpr int dense_tiles(int nt) { return nt <= 2 ? 2 : nt <= 4 ? nt : nt <= 6 ? 6 : 8; }
-// LDS of a dense level of nt tiles of 16 rows (the matrix and a block)
-__host__ __device__ constexpr int dense_lds_bytes(int nt) { return 8 * (16 * nt * (16 * nt) + 16 * nt * 16); }
+// tiles a side of the kernel that takes a level of nt
+__host__ __device__ constexpr int dense_tiles(int nt) {
+    return nt <= 2 ? 2 : nt <= 4 ? nt : nt <= 6 ? 6 : nt <= 8 ? 8 : nt <= 9 ? 9 : 11;
+}
+// its LDS: the lower triangle of tiles (or a block, if larger) and a block
+__host__ __device__ constexpr int dense_lds_bytes(int nt) { return 8 * (nt * (nt + 1) / 2 * 256 + 16 * nt * 16); }
 
 // Levels jhi down to jlo, each of at most kDenseBlockN vertices, as dense
 // matrices in one workgroup (err = 2 on a level that does not fit).
@@ -1302,12 +1380,14 @@ __global__ void __launch_bounds__(kBlockRegsThreads)
         in.maxit = L.kfix > 0 ? L.kfix : Jb.maxit;
         LevelState o{};
         const int nt = (L.n + 15) / 16;
-        if (L.n < 1 || nt > 8 || dense_lds_bytes(dense_tiles(nt)) > lds_budget) o.err = 2;
+        if (L.n < 1 || nt > 11 || dense_lds_bytes(dense_tiles(nt)) > lds_budget) o.err = 2;
         else if (nt <= 2) dense_level<2>(L, in, lds, red, part, o);
         else if (nt == 3) dense_level<3>(L, in, lds, red, part, o);
         else if (nt == 4) dense_level<4>(L, in, lds, red, part, o);
         else if (nt <= 6) dense_level<6>(L, in, lds, red, part, o);
-        else dense_level<8>(L, in, lds, red, part, o);
+        else if (nt <= 8) dense_level<8>(L, in, lds, red, part, o);
+        else if (nt == 9) dense_level<9>(L, in, lds, red, part, o);
+        else dense_level<11>(L, in, lds, red, part, o);
         if (threadIdx.x == 0) {
             o.ticks = wall_clock64() - t_start;
             Jb.st[j] = o;
@@ -1357,13 +1437,13 @@ int refine_block_lds_budget() {
         if (hipGetDevice(&dev) == hipSuccess)
             (void)hipDeviceGetAttribute(&maxsh, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
         size_t stat = 0;
-        for (int r = 0; r < kBlockKinds; ++r) {
+        for (int r = 0; r < kBlockDense; ++r) {
             hipFuncAttributes fa;
             if (hipFuncGetAttributes(&fa, block_kernel(r)) == hipSuccess) stat = std::max(stat, fa.sharedSizeBytes);
         }
         long b = std::min<long>(kBlockLdsMax, (long)maxsh - (long)stat - 256);
         b = std::max<long>(b, 0);
-        for (int r = 0; r < kBlockKinds; ++r) {
+        for (int r = 0; r < kBlockDense; ++r) {
             if (b > 65536 - (long)stat - 256 &&
                 hipFuncSetAttribute(block_kernel(r), hipFuncAttributeMaxDynamicSharedMemorySize, (int)b) != hipSuccess) {
                 (void)hipGetLastError();
@@ -1375,11 +1455,32 @@ int refine_block_lds_budget() {
     return budget;
 }
 
-int dense_block_lds(int n) { return dense_lds_bytes(dense_tiles((n + 15) / 16)); }
+// The dense kernel asks for LDS beyond the other kernels' budget.
+int dense_block_budget() {
+    static const int budget = [] {
+        int dev = 0, maxsh = 65536;
+        if (hipGetDevice(&dev) == hipSuccess)
+            (void)hipDeviceGetAttribute(&maxsh, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+        hipFuncAttributes fa;
+        if (hipFuncGetAttributes(&fa, (const void*)k_block_dense) != hipSuccess) return 0;
+        const int b = std::min(maxsh - (int)fa.sharedSizeBytes, dense_lds_bytes(dense_tiles(kDenseBlockN / 16)));
+        if (hipFuncSetAttribute((const void*)k_block_dense, hipFuncAttributeMaxDynamicSharedMemorySize, b) !=
+            hipSuccess) {
+            (void)hipGetLastError();
+            return 0;
+        }
+        return b;
+    }();
+    return budget;
+}
+
+bool dense_block_fits(int n) {
+    return n <= kDenseBlockN && dense_lds_bytes(dense_tiles((n + 15) / 16)) <= dense_block_budget();
+}
 
 hipError_t launch_block_jobs(const BlockJob* jobs, int njobs, int kind, hipStream_t s) {
     if (kind < 0 || kind >= kBlockKinds) return hipErrorInvalidValue;
-    const int budget = refine_block_lds_budget();
+    const int budget = kind == kBlockDense ? dense_block_budget() : refine_block_lds_budget();
     void* args[] = {(void*)&jobs, (void*)&budget};
     return hipLaunchKernel(block_kernel(kind), dim3(njobs), dim3(kind ? kBlockRegsThreads : kBlockKernelThreads), args,
                            (size_t)budget, s);
