@@ -232,6 +232,273 @@ __global__ void __launch_bounds__(kBlkCheck) k_blk_norm(const BlkJob* __restrict
     }
 }
 
+// ------------------------------------------------- small levels, one workgroup
+//
+// A step of a small level is microseconds of work between two launches of
+// about 10 us each (the sums of a step, 34 values over every workgroup, and
+// a Cholesky factorisation on one thread): 115 vertices took 23 us a step.
+// Levels of at most kBlkSmallN vertices therefore run all their steps, level
+// after level, inside one workgroup: a row per thread, both blocks in LDS,
+// one barrier a step.  The sums (1^T Z, Z^T Z and the upper part of Z^T V,
+// all that the test reads; 1^T V is zero to rounding) are folded across the
+// lanes of a wavefront by halves, so that a lane ends with a few of them,
+// and every wavefront adds the posts and factors the Gram matrix itself.
+// Four columns on a 200000-vertex geometric graph, whose levels of 891 down
+// to 42 vertices take 3057 of 3276 steps: 92 -> 16 ms.  Past 1024 vertices a
+// thread has more than one row and the launches' share falls (2527 vertices:
+// 94 steps), so larger levels keep one launch per step.
+constexpr int kBlkSmallThreads = 1024;
+
+template <int P>
+struct BlkSmall {
+    static constexpr int kTri = P * (P + 1) / 2;
+    static constexpr int kUsed = P + 2 * kTri;
+    static constexpr int kNV = P == 4 ? 24 : P == 3 ? 16 : P == 2 ? 8 : 4;  // padded
+    static constexpr int kLeft = P == 4 ? 3 : 1;                            // a lane's values after the folds
+    static constexpr int kFolds = P == 4 ? 3 : P == 3 ? 4 : P == 2 ? 3 : 2;
+};
+
+// one exchange: lanes with `up` keep the upper half of the first 2 H values
+template <int CTRL, int H, int NV>
+__device__ __forceinline__ void blk_fold(double (&v)[NV], bool up) {
+#pragma unroll
+    for (int q = 0; q < H; ++q) {
+        const double keep = up ? v[q + H] : v[q];
+        const double send = up ? v[q] : v[q + H];
+        v[q] = keep + dpp_move<CTRL>(send);
+    }
+}
+
+// Sums of v over the workgroup's first nw wavefronts, the same in every
+// thread.  The partner of lane i is i ^ 15, i ^ 7, i ^ 3, i ^ 1 in turn, so
+// partners hold the same values; part: 2 x 16 x kNV doubles, by parity.
+template <int P>
+__device__ __forceinline__ void blk_small_sums(double (&v)[BlkSmall<P>::kNV], double* part, int& parity, int nw) {
+    constexpr int NV = BlkSmall<P>::kNV, LEFT = BlkSmall<P>::kLeft, F = BlkSmall<P>::kFolds;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double* slot = part + parity * 16 * NV;
+    if (wv < nw) {
+        blk_fold<0x140, NV / 2>(v, (lane & 8) != 0);
+        blk_fold<0x141, NV / 4>(v, (lane & 4) != 0);
+        if constexpr (F >= 3) blk_fold<0x1B, NV / 8>(v, (lane & 2) != 0);
+        if constexpr (F >= 4) blk_fold<0xB1, NV / 16>(v, (lane & 1) != 0);
+#pragma unroll
+        for (int q = 0; q < LEFT; ++q) {
+            if constexpr (F < 3) v[q] += dpp_move<0x1B>(v[q]);
+            if constexpr (F < 4) v[q] += dpp_move<0xB1>(v[q]);
+            v[q] = pair_sum_rows<32>(pair_sum_rows<16>(v[q]));
+        }
+        constexpr int STEP = 16 >> F;  // lanes of a row with the same values
+        if (lane < 16 && lane % STEP == 0) {
+#pragma unroll
+            for (int q = 0; q < LEFT; ++q) slot[wv * NV + (lane / STEP) * LEFT + q] = v[q];
+        }
+    }
+    __syncthreads();
+    double t = 0.0;
+    if (lane < NV)
+        for (int w = 0; w < nw; ++w) t += slot[w * NV + lane];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) v[q] = read_lane(t, q);
+    parity ^= 1;
+}
+
+// As chol_inv, with reciprocal square roots in place of square roots and
+// divisions; tri: upper triangle of Z^T Z, row by row.
+template <int P>
+__device__ __forceinline__ bool blk_small_chol(const double* colsum, const double* tri, double n, double inv_n,
+                                               double (&mu)[P], double (&rinv)[P][P]) {
+    double R[P][P];
+    bool ok = true;
+#pragma unroll
+    for (int r = 0; r < P; ++r) mu[r] = colsum[r] * inv_n;
+    int t = 0;
+#pragma unroll
+    for (int r = 0; r < P; ++r)
+#pragma unroll
+        for (int c = r; c < P; ++c, ++t) R[r][c] = tri[t] - n * mu[r] * mu[c];
+#pragma unroll
+    for (int c = 0; c < P; ++c) {
+        double s = R[c][c];
+#pragma unroll
+        for (int k = 0; k < c; ++k) s -= R[k][c] * R[k][c];
+        ok = ok && s > 0.0;
+        const double id = fast_rsq(s);
+        rinv[c][c] = id;
+#pragma unroll
+        for (int j = c + 1; j < P; ++j) {
+            double u = R[c][j];
+#pragma unroll
+            for (int k = 0; k < c; ++k) u -= R[k][c] * R[k][j];
+            R[c][j] = u * id;
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < P; ++c)
+#pragma unroll
+        for (int r = c - 1; r >= 0; --r) {
+            double s = 0.0;
+#pragma unroll
+            for (int k = r + 1; k <= c; ++k) s += R[r][k] * rinv[k][c];
+            rinv[r][c] = -s * rinv[r][r];
+        }
+    return ok;
+}
+
+// w (row-major P per row) times the upper-triangular rinv
+template <int P>
+__device__ __forceinline__ void blk_small_right(const double (&y)[P], const double (&rinv)[P][P], double (&z)[P]) {
+#pragma unroll
+    for (int c = 0; c < P; ++c) {
+        double s = 0.0;
+#pragma unroll
+        for (int r = 0; r <= c; ++r) s += y[r] * rinv[r][c];
+        z[c] = s;
+    }
+}
+
+// LDS: both blocks, then rows, columns and weights if they fit
+template <int P>
+constexpr size_t blk_small_fixed(int n) { return 16 * (size_t)P * (size_t)n; }
+__host__ __device__ inline size_t blk_small_csr(int n, int64_t nnz) {
+    return 8 * (size_t)nnz + 4 * (((size_t)n + 2) & ~(size_t)1) + 2 * (((size_t)nnz + 3) & ~(size_t)3);
+}
+
+// Levels jhi down to jlo of a hierarchy (jobs[j], each of at most kBlkSmallN
+// vertices).  The last block of a level is left in its W0.
+template <int P>
+__global__ void __launch_bounds__(kBlkSmallThreads) k_blk_small(const BlkJob* __restrict__ jobs, int jhi, int jlo,
+                                                                int lds_bytes) {
+    using B = BlkSmall<P>;
+    extern __shared__ double lds[];
+    __shared__ double part[2 * 16 * B::kNV];
+    const int i = (int)threadIdx.x;
+    int parity = 0;
+    for (int j = jhi; j >= jlo; --j) {
+        const BlkJob J = jobs[j];
+        const int n = J.n;
+        const int nw = (n + 63) / 64;
+        const bool row = i < n;
+        const double dn = (double)n, inv_n = 1.0 / dn;
+        const int a0 = row ? gld(J.rp, i) : 0, b0 = row ? gld(J.rp, i + 1) : 0;
+        const int nnz = gld(J.rp, n);
+        double* w0 = lds;
+        double* w1 = lds + (size_t)P * n;
+        double* sw = w1 + (size_t)P * n;
+        uint16_t* sc = (uint16_t*)(sw + nnz);
+        const bool staged = blk_small_fixed<P>(n) + blk_small_csr(n, nnz) <= (size_t)lds_bytes;
+        __syncthreads();  // the level before has been written out
+        if (staged)
+            for (int e = i; e < nnz; e += kBlkSmallThreads) {
+                sst(sw, e, gld(J.w, e));
+                sst(sc, e, (uint16_t)gld(J.col, e));
+            }
+        // prolongation
+        double acc[B::kNV];
+#pragma unroll
+        for (int q = 0; q < B::kNV; ++q) acc[q] = 0.0;
+        if (row) {
+            const BlkCtl* cc = J.cctl;
+            const double* cw = (cc->cur ? J.cW1 : J.cW0) + (size_t)gld(J.agg, i) * P;
+            double v[P];
+            to_v<P>(cw, cc->mu, cc->rinv, v);
+            int t = P;
+#pragma unroll
+            for (int r = 0; r < P; ++r) {
+                sst(w0, i * P + r, v[r]);
+                acc[r] = v[r];
+#pragma unroll
+                for (int c = r; c < P; ++c) acc[t++] = v[r] * v[c];
+            }
+        }
+        blk_small_sums<P>(acc, part, parity, nw);
+        double mu[P], rinv[P][P];
+        int k = 0, hit = blk_small_chol<P>(acc, acc + P, dn, inv_n, mu, rinv) ? 0 : 2, cur = 0;
+        double minu = 0.0;
+        const double g = J.g;
+        while (hit == 0) {
+            const double* win = cur ? w1 : w0;
+            double* wout = cur ? w0 : w1;
+#pragma unroll
+            for (int q = 0; q < B::kNV; ++q) acc[q] = 0.0;
+            if (row) {
+                double wi[P], y[P], d[P], z[P], v[P];
+#pragma unroll
+                for (int r = 0; r < P; ++r) {
+                    wi[r] = sld(win, i * P + r);
+                    d[r] = wi[r] - mu[r];
+                    y[r] = g * d[r];
+                }
+                auto entry = [&](int c, double a) {
+#pragma unroll
+                    for (int r = 0; r < P; ++r) y[r] += a * (sld(win, c * P + r) - wi[r]);
+                };
+                if (staged) {
+#pragma unroll 2
+                    for (int e = a0; e < b0; ++e) entry((int)sld(sc, e), sld(sw, e));
+                } else {
+#pragma unroll 4
+                    for (int e = a0; e < b0; ++e) entry(gld(J.col, e), gld(J.w, e));
+                }
+                blk_small_right<P>(y, rinv, z);
+                blk_small_right<P>(d, rinv, v);
+                int t = P;
+#pragma unroll
+                for (int r = 0; r < P; ++r) {
+                    sst(wout, i * P + r, z[r]);
+                    acc[r] = z[r];
+#pragma unroll
+                    for (int c = r; c < P; ++c) acc[t++] = z[r] * z[c];
+                }
+#pragma unroll
+                for (int r = 0; r < P; ++r)
+#pragma unroll
+                    for (int c = r; c < P; ++c) acc[t++] = z[r] * v[c];
+            }
+            blk_small_sums<P>(acc, part, parity, nw);
+            const bool ok = blk_small_chol<P>(acc, acc + P, dn, inv_n, mu, rinv);
+            // (u_c, v_c) = (R^{-T} Z^T V)_cc
+            minu = 2.0;
+#pragma unroll
+            for (int c = 0; c < P; ++c) {
+                double d = 0.0;
+                int t = P + B::kTri;
+#pragma unroll
+                for (int r = 0; r < P; ++r)
+#pragma unroll
+                    for (int q = r; q < P; ++q, ++t)
+                        if (q == c) d += rinv[r][c] * acc[t];
+                minu = d < minu ? d : minu;
+            }
+            ++k;
+            cur ^= 1;
+            if (!ok) hit = 2;
+            else if (J.kfix > 0) {
+                if (k >= J.kfix) break;
+            } else if (!(minu < 1.0 - J.tol)) break;
+            else if (k >= J.maxit) hit = 1;
+        }
+        const double* w = cur ? w1 : w0;
+        for (int q = i; q < n * P; q += kBlkSmallThreads) gst(J.W0, q, sld(w, q));
+        if (i == 0) {
+            BlkCtl s{};
+#pragma unroll
+            for (int r = 0; r < P; ++r) {
+                s.mu[r] = mu[r];
+#pragma unroll
+                for (int c = 0; c < P; ++c) s.rinv[r * P + c] = c >= r ? rinv[r][c] : 0.0;
+            }
+            s.k = k;
+            s.cur = 0;
+            s.done = 1;
+            s.hit = hit;
+            s.minutv = minu;
+            *J.ctl = s;
+        }
+        __syncthreads();
+    }
+}
+
 // one step of orthogonal iteration: W[cur] -> W[cur ^ 1]
 template <int P>
 __global__ void __launch_bounds__(kBlkThreads) k_blk_step(const BlkJob* __restrict__ jp) {
@@ -436,7 +703,48 @@ hipError_t blk_launch(int what, const BlkJob* dj, const BlkJob& hj, double* X, c
     return hipGetLastError();
 }
 
+template <int P>
+int blk_small_lds() {
+    static const int bytes = [] {
+        int dev = 0, maxsh = 65536;
+        if (hipGetDevice(&dev) == hipSuccess)
+            (void)hipDeviceGetAttribute(&maxsh, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+        hipFuncAttributes fa;
+        if (hipFuncGetAttributes(&fa, (const void*)k_blk_small<P>) != hipSuccess) return 0;
+        const int b = (maxsh - (int)fa.sharedSizeBytes - 256) & ~255;
+        if (hipFuncSetAttribute((const void*)k_blk_small<P>, hipFuncAttributeMaxDynamicSharedMemorySize, b) !=
+            hipSuccess) {
+            (void)hipGetLastError();
+            return 0;
+        }
+        return b;
+    }();
+    return bytes;
+}
+
+template <int P>
+hipError_t blk_small_launch(const BlkJob* dj, int jhi, int jlo, hipStream_t s) {
+    const int b = blk_small_lds<P>();
+    hipLaunchKernelGGL(k_blk_small<P>, dim3(1), dim3(kBlkSmallThreads), b, s, dj, jhi, jlo, b);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+bool blk_small_level(int p, int n) {
+    const int b = p == 1 ? blk_small_lds<1>() : p == 2 ? blk_small_lds<2>() : p == 3 ? blk_small_lds<3>() : blk_small_lds<4>();
+    return n <= kBlkSmallN && 16 * (int64_t)p * n <= b;
+}
+
+hipError_t launch_blk_small(int p, const BlkJob* dj, int jhi, int jlo, hipStream_t s) {
+    switch (p) {
+        case 1: return blk_small_launch<1>(dj, jhi, jlo, s);
+        case 2: return blk_small_launch<2>(dj, jhi, jlo, s);
+        case 3: return blk_small_launch<3>(dj, jhi, jlo, s);
+        case 4: return blk_small_launch<4>(dj, jhi, jlo, s);
+        default: return hipErrorInvalidValue;
+    }
+}
 
 int blk_parts(int p) {
     const int tri = p * (p + 1) / 2;

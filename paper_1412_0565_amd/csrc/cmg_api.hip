@@ -1935,7 +1935,11 @@ cmg_status block_impl(cmg_ctx* c, int p, double* lambdas, void* X, cmg_memspace 
     cmg_status st = blk_plan(c, p);
     if (st != CMG_OK) return st;
     CK(launch_blk(kBlkCoarse, p, nullptr, c->blk_jobs[J], nullptr, c->d_V, c->d_ev, c->d_idx, s));
-    for (int j = J - 1; j >= 0; --j) {
+    // the small levels in one workgroup, the larger ones one launch per step
+    int j = J - 1;
+    while (j >= 0 && blk_small_level(p, c->lv[j].n)) --j;
+    if (j < J - 1) CK(launch_blk_small(p, c->d_blk_jobs, J - 1, j + 1, s));
+    for (; j >= 0; --j) {
         CK(launch_blk(kBlkProlong, p, c->d_blk_jobs + j, c->blk_jobs[j], nullptr, nullptr, nullptr, nullptr, s));
         st = blk_steps(c, j, p, s);
         if (st != CMG_OK) return st;

@@ -280,6 +280,11 @@ int blk_parts(int p);
 // (n x P column-major), Rayleigh quotients and residuals).
 hipError_t launch_blk(int what, int p, const BlkJob* dj, const BlkJob& hj, double* X, const double* V,
                       const double* ev, const int32_t* idx, hipStream_t s);
+// Levels jhi down to jlo, each one that blk_small_level accepts, in one
+// workgroup (job table dj indexed by level).
+constexpr int kBlkSmallN = 1024;
+bool blk_small_level(int p, int n);
+hipError_t launch_blk_small(int p, const BlkJob* dj, int jhi, int jlo, hipStream_t s);
 // ---- bisect.hip: recursive spectral bisection (one depth of all parts at once)
 hipError_t launch_rsb_keys(int n, const int32_t* part, unsigned long long* keys, hipStream_t s);
 hipError_t launch_rsb_perm(int n, const unsigned long long* keys, int32_t* perm, int32_t* pos, int32_t* first,
