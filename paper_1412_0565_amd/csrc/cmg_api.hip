@@ -1824,6 +1824,11 @@ cmg_status ensure_flags(cmg_ctx* c) {
 }
 
 // Buffers and job table of the block refinement for p columns (once per p).
+// rows + entries per workgroup of a block step (a pass or two of its 256
+// threads), and the most workgroups: one workgroup adds their sums, 1024 of
+// them in about the time of one
+constexpr int64_t kBlkWork = 1024, kBlkMaxGroups = 1024;
+
 cmg_status blk_plan(cmg_ctx* c, int p) {
     if (c->blk_p == p) return CMG_OK;
     const int J = (int)c->lv.size() - 1;
@@ -1837,8 +1842,8 @@ cmg_status blk_plan(cmg_ctx* c, int p) {
         const HostLevel& L = c->lv[j];
         BlkJob b{};
         b.n = L.n;
-        const int64_t nb = ((int64_t)L.n + L.nnz + kStepWork - 1) / kStepWork;
-        b.nb = (int)std::min<int64_t>(std::max<int64_t>(nb, 1), 65535);
+        const int64_t nb = ((int64_t)L.n + L.nnz + kBlkWork - 1) / kBlkWork;
+        b.nb = (int)std::min<int64_t>(std::max<int64_t>(nb, 1), kBlkMaxGroups);
         maxnb = std::max(maxnb, b.nb);
         b.rp = L.rp;
         b.col = L.col;
