@@ -750,7 +750,7 @@ bool chain_level(const HostLevel& L) { return L.n <= kChainMaxN && L.nnz <= kCha
 // Coarsens level j0 and the levels below it in one workgroup.  *next = -1
 // if the hierarchy is complete, else the index of a level left to the grid
 // kernels (a coarse row too long for the single-workgroup Galerkin step).
-cmg_status coarsen_chain(cmg_ctx* c, SetupTmp& t, int j0, int* next) {
+cmg_status coarsen_chain(cmg_ctx* c, int j0, int* next) {
     Range range("cmg coarsen levels from %d in one workgroup", j0);
     HostLevel L = c->lv[j0];
     hipStream_t s = c->stream;
@@ -779,9 +779,6 @@ cmg_status coarsen_chain(cmg_ctx* c, SetupTmp& t, int j0, int* next) {
     job.seed = c->opt.seed;
     job.coarsest_n = c->opt.coarsest_n;
     job.max_levels = max_levels;
-    // scratch: the level-0 setup buffers (nnz0 >= nnz)
-    job.mb = (int32_t*)t.k1;
-    job.mw = t.v0;
     ALLOC(job.ai32, int32_t, i32cap);
     job.ai32_cap = i32cap;
     ALLOC(job.acol, int32_t, cw);
@@ -1504,7 +1501,7 @@ cmg_status setup_impl(cmg_ctx* c, int32_t n, int64_t nnz, const int32_t* row_ptr
         // the single-workgroup chain implements HEC only
         if (!grid_only && c->opt.coarsen == 0 && chain_level(c->lv[j])) {
             int next = -1;
-            st = coarsen_chain(c, t, j, &next);
+            st = coarsen_chain(c, j, &next);
             if (st != CMG_OK) return st;
             if (next < 0) break;
             j = next;

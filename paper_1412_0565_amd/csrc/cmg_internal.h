@@ -23,7 +23,7 @@ constexpr unsigned kNonUnit = 16u;
 constexpr int kChainThreads = 1024;
 constexpr int kChainMaxN = 8192;         // levels with at most this many vertices
 constexpr int64_t kChainMaxNnz = 262144; // ... and at most this many entries
-constexpr int kChainMaxRow = 1024;       // longest coarse row (member entries) one thread forms
+constexpr int kChainMaxRow = 1024;       // most fine entries of a coarse row
 
 // One level visited by the chain: its row information, and where its
 // arrays were written (offsets into the arenas; -1 for the first level,
@@ -46,10 +46,6 @@ struct ChainJob {
     uint64_t seed;
     int32_t coarsest_n;
     int32_t max_levels;  // levels that may be visited, the first included
-    // scratch of nnz0 entries: coarse rows that outgrow a thread's registers
-    // or wait for their row pointers
-    int32_t* mb;
-    double* mw;
     // arenas for the levels produced: agg and row pointers (ai32), columns
     // and weights (acol, aw)
     int32_t* ai32;

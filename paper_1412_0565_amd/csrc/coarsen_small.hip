@@ -7,9 +7,8 @@
 // launches and 7 host synchronisations per level; on small levels those
 // gaps, not the work, set the setup time.
 //
-// The Galerkin product is formed per coarse row: the members of aggregate
-// a are visited in increasing index and their entries in CSR order, so the
-// contributions to each coarse entry (a, b) are added in fine CSR order,
+// The Galerkin product sorts the fine entries of each coarse row in LDS, so
+// the contributions to each coarse entry (a, b) are added in fine CSR order,
 // the order the grid path's stable sort produces.  Results are bit-exact
 // with the grid path and the oracle (integer and real weights alike).
 #include "cmg_internal.h"
@@ -79,51 +78,61 @@ __device__ void block_max4(double (&m)[4], double* sm) {
     __syncthreads();
 }
 
-// Columns a thread keeps in registers while it forms a coarse row.
-constexpr int kChainSlots = 12;
 // Longest fine row of a level this kernel coarsens (measured on MI355X:
 // 3D-grid levels with 27-47 entries per row took 0.27-1.9 ms here against
 // a few hundred microseconds on the grid kernels).
 constexpr int kChainLongRow = 24;
 
 // Everything per vertex or aggregate lives in LDS (16-bit ids, as a level
-// has at most kChainMaxN = 8192 vertices); only the CSR arrays, the arenas
-// of the levels produced and the rows that outgrow the register slots are
-// in memory.  A phase is a handful of dependent accesses per thread, so its
-// time is their latency: one workgroup on arrays in memory took 177 us for
-// the four levels below 992 vertices and 459 us for the five below 6016.
-// The 8-byte slots of the greedy rounds are dead once the matching stands,
-// and their space then holds the arrays of the aggregates.
+// has at most kChainMaxN = 8192 vertices); only the CSR arrays and the arenas
+// of the levels produced are in memory.  The 8-byte slots of the greedy
+// rounds are dead once the matching stands, as are the arrays of a phase once
+// the next one stands; `tile` takes their space for the coarse rows.
+constexpr int kChainTile = 13 * kChainThreads;  // contributions held at once
+constexpr int kChainRuns = kChainTile / 64;
 struct ChainLds {
     union {
         unsigned long long slot[kChainMaxN];
         struct {
-            uint16_t rank[kChainMaxN];          // aggregate opened by a vertex
             uint16_t agg[kChainMaxN];
-            int32_t astart[kChainMaxN / 2 + 1];  // first member of each aggregate
-            int32_t acnt[kChainMaxN / 2];
+            union {
+                struct {
+                    uint16_t rank[kChainMaxN];  // aggregate opened by a vertex
+                    int32_t astart[kChainMaxN / 2];  // first member of each aggregate
+                    int32_t acnt[kChainMaxN / 2];
+                    union {
+                        uint16_t h[kChainMaxN];
+                        uint16_t members[kChainMaxN];
+                    } v;
+                    union {
+                        struct {
+                            uint8_t live[kChainMaxN], state[kChainMaxN];
+                        } f;
+                        int32_t rcount[kChainMaxN / 2];
+                    } l;
+                } m;
+                struct {
+                    uint32_t key[kChainTile];   // coarse column << 19 | fine entry
+                    uint16_t row[kChainTile];
+                    uint16_t head[kChainTile];  // slots that open a coarse entry
+                } tile;
+            } t;
         } a;
     } u;
     union {
-        uint16_t h[kChainMaxN];
-        uint16_t members[kChainMaxN];
-    } v;
-    union {
         uint16_t pair[kChainMaxN];
         int32_t afill[kChainMaxN / 2];
+        uint16_t off[kChainMaxN];  // a vertex's first slot within its coarse row
     } p;
     union {
         uint16_t root[kChainMaxN];
-        int32_t soff[kChainMaxN / 2];  // scratch offset of a coarse row
+        int32_t soff[kChainMaxN / 2 + 1];  // first slot of a coarse row
     } r;
-    union {
-        struct {
-            uint8_t live[kChainMaxN], state[kChainMaxN];
-        } f;
-        int32_t rcount[kChainMaxN / 2];
-    } l;
 };
-static_assert(sizeof(ChainLds) <= 140 * 1024, "one workgroup's LDS");
+static_assert(offsetof(ChainLds, u.a.t.m.v) >= sizeof(unsigned long long) * kChainMaxN, "alive beside the slots");
+static_assert(sizeof(ChainLds) <= 156 * 1024, "one workgroup's LDS");
+static_assert(kChainMaxN / 2 < 0x1fff && kChainMaxNnz <= 1 << 18 && kChainMaxRow + 3 <= kChainTile, "slot keys");
+constexpr uint32_t kChainDrop = 0x1fffu << 19;  // keys from here on: inside the aggregate, or a row's padding
 
 // a thread's walk over entries [a, b): `many` loads in flight, in order
 template <int U, class F>
@@ -144,10 +153,13 @@ __device__ __forceinline__ void chain_walk(const int32_t* col, const double* w, 
 }
 
 __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
-    extern __shared__ double lds_raw[];
+    extern __shared__ __align__(16) double lds_raw[];
     ChainLds& S = *(ChainLds*)lds_raw;
+    auto& M = S.u.a.t.m;
+    auto& R = S.u.a.t.tile;
     __shared__ int sh[17];
     __shared__ double sm[4 * 16];
+    __shared__ int runs[kChainRuns];
     __shared__ int s_bad;
     __shared__ int s_iso;
     const int tid = threadIdx.x, T = blockDim.x;
@@ -184,7 +196,7 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
                 bc = v;
                 s_iso = 1;
             }
-            S.v.h[v] = (uint16_t)bc;
+            M.v.h[v] = (uint16_t)bc;
             m4[0] = fmax(m4[0], 2.0 * d);
             m4[1] = fmax(m4[1], bw);
         }
@@ -223,39 +235,39 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
         // ---- HEC: candidates, greedy rounds
         for (int v = tid; v < n; v += T) {
             S.p.pair[v] = (uint16_t)v;
-            S.l.f.live[v] = (hec_key(J.seed, level, v) < hec_key(J.seed, level, S.v.h[v])) ? 1 : 0;
-            S.l.f.state[v] = 0;
+            M.l.f.live[v] = (hec_key(J.seed, level, v) < hec_key(J.seed, level, M.v.h[v])) ? 1 : 0;
+            M.l.f.state[v] = 0;
             S.u.slot[v] = kNoKeyC;
         }
         __syncthreads();
         int rounds = 0;
         while (true) {
             for (int v = tid; v < n; v += T) {
-                if (!S.l.f.live[v]) continue;
+                if (!M.l.f.live[v]) continue;
                 const unsigned long long kv = hec_key(J.seed, level, v);
                 atomicMin(&S.u.slot[v], kv);
-                atomicMin(&S.u.slot[S.v.h[v]], kv);
+                atomicMin(&S.u.slot[M.v.h[v]], kv);
             }
             __syncthreads();
             for (int v = tid; v < n; v += T) {
-                if (!S.l.f.live[v]) continue;
+                if (!M.l.f.live[v]) continue;
                 const unsigned long long kv = hec_key(J.seed, level, v);
-                const int m = S.v.h[v];
+                const int m = M.v.h[v];
                 if (S.u.slot[v] == kv && S.u.slot[m] == kv) {
-                    S.l.f.state[v] = kSeedC;
-                    S.l.f.state[m] = kPartnerC;
+                    M.l.f.state[v] = kSeedC;
+                    M.l.f.state[m] = kPartnerC;
                     S.p.pair[v] = (uint16_t)v;
                     S.p.pair[m] = (uint16_t)v;
-                    S.l.f.live[v] = 0;
+                    M.l.f.live[v] = 0;
                 }
             }
             __syncthreads();
             int alive = 0;
             for (int v = tid; v < n; v += T) {
-                if (!S.l.f.live[v]) continue;
-                const int m = S.v.h[v];
-                if (S.l.f.state[v] != 0 || S.l.f.state[m] != 0) {
-                    S.l.f.live[v] = 0;
+                if (!M.l.f.live[v]) continue;
+                const int m = M.v.h[v];
+                if (M.l.f.state[v] != 0 || M.l.f.state[m] != 0) {
+                    M.l.f.live[v] = 0;
                 } else {
                     S.u.slot[v] = kNoKeyC;
                     S.u.slot[m] = kNoKeyC;
@@ -269,14 +281,14 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
         // ---- attach: follow h to a matched vertex
         for (int v = tid; v < n; v += T) {
             int r = v;
-            for (int guard = 0; guard < n && S.l.f.state[r] == 0; ++guard) r = S.v.h[r];
+            for (int guard = 0; guard < n && M.l.f.state[r] == 0; ++guard) r = M.v.h[r];
             S.r.root[v] = S.p.pair[r];
         }
         __syncthreads();
         // number the opening vertices (the slots are dead from here on)
         const int nc = chain_scan(
-            n, sh, [&](int v) { return S.l.f.state[v] == kSeedC ? 1 : 0; },
-            [&](int v, int q) { S.u.a.rank[v] = (uint16_t)q; });
+            n, sh, [&](int v) { return M.l.f.state[v] == kSeedC ? 1 : 0; },
+            [&](int v, int q) { M.rank[v] = (uint16_t)q; });
         if (nc < 2) {
             collapsed = 1;
             stop_reason = 2;
@@ -295,29 +307,29 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
         int32_t* agg = J.ai32 + i32_used;
         hd.agg_off = i32_used;
         for (int a = tid; a < nc; a += T) {
-            S.u.a.acnt[a] = 0;
+            M.acnt[a] = 0;
             S.p.afill[a] = 0;
         }
         if (tid == 0) s_bad = 0;
         __syncthreads();
         // ---- members of each aggregate, in increasing vertex index
         for (int v = tid; v < n; v += T) {
-            const int a = S.u.a.rank[S.r.root[v]];
+            const int a = M.rank[S.r.root[v]];
             S.u.a.agg[v] = (uint16_t)a;
             gst(agg, v, (int32_t)a);
-            atomicAdd(&S.u.a.acnt[a], 1);
+            atomicAdd(&M.acnt[a], 1);
         }
         __syncthreads();
         chain_scan(
-            nc, sh, [&](int a) { return S.u.a.acnt[a]; }, [&](int a, int q) { S.u.a.astart[a] = q; });
+            nc, sh, [&](int a) { return M.acnt[a]; }, [&](int a, int q) { M.astart[a] = q; });
         for (int v = tid; v < n; v += T) {
             const int a = S.u.a.agg[v];
-            S.v.members[S.u.a.astart[a] + atomicAdd(&S.p.afill[a], 1)] = (uint16_t)v;
+            M.v.members[M.astart[a] + atomicAdd(&S.p.afill[a], 1)] = (uint16_t)v;
         }
         __syncthreads();
         for (int a = tid; a < nc; a += T) {
-            uint16_t* ms = S.v.members + S.u.a.astart[a];
-            const int cnt = S.u.a.acnt[a];
+            uint16_t* ms = M.v.members + M.astart[a];
+            const int cnt = M.acnt[a];
             for (int i = 1; i < cnt; ++i) {
                 const uint16_t x = ms[i];
                 int j = i - 1;
@@ -327,10 +339,14 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
                 }
                 ms[j + 1] = x;
             }
-            int64_t deg = 0;
-            for (int i = 0; i < cnt; ++i) deg += gld(rp, (int)ms[i] + 1) - gld(rp, (int)ms[i]);
+            int deg = 0;  // at most nnz <= kChainMaxNnz
+            for (int i = 0; i < cnt; ++i) {
+                const int m = ms[i];
+                S.p.off[m] = (uint16_t)deg;
+                deg += gld(rp, m + 1) - gld(rp, m);
+            }
             if (deg > kChainMaxRow) s_bad = 1;
-            S.l.rcount[a] = (int32_t)deg;
+            M.l.rcount[a] = (deg + 3) & ~3;
         }
         __syncthreads();
         if (s_bad) {
@@ -341,147 +357,149 @@ __global__ void __launch_bounds__(kChainThreads) k_coarsen_chain(ChainJob J) {
             if (tid == 0) J.hdr[k] = hd;
             break;
         }
-        chain_scan(
-            nc, sh, [&](int a) { return S.l.rcount[a]; }, [&](int a, int q) { S.r.soff[a] = q; });
+        {
+            const int all = chain_scan(
+                nc, sh, [&](int a) { return M.l.rcount[a]; }, [&](int a, int q) { S.r.soff[a] = q; });
+            if (tid == 0) S.r.soff[nc] = all;
+        }
         int32_t* rpc = J.ai32 + i32_used + n;
         int32_t* colc = J.acol + cw_used;
         double* wc = J.aw + cw_used;
-        // ---- Galerkin: one thread per coarse row, contributions added in
-        // fine CSR order, row sorted by coarse column.  The row is formed in
-        // the thread's register slots; a row with more distinct columns
-        // moves to its global scratch and goes on there.  Where every row
-        // has a thread of its own it stays in the registers until the
-        // row lengths are scanned; else it waits in the scratch.
-        const bool once = nc <= T;
-        int rb[kChainSlots];
-        double rw[kChainSlots];
-        int len = 0;
-        bool in_regs = true;
-        for (int a = tid; a < nc; a += T) {
-            const uint16_t* ms = S.v.members + S.u.a.astart[a];
-            const int cnt = S.u.a.acnt[a];
-            int32_t* mb = J.mb + S.r.soff[a];
-            double* mw = J.mw + S.r.soff[a];
-            // the row in registers: columns rb[0..len) (unused: INT_MAX) and
-            // their sums; every slot operation is unrolled and branch-free
-#pragma unroll
-            for (int q = 0; q < kChainSlots; ++q) {
-                rb[q] = 0x7fffffff;
-                rw[q] = 0.0;
-            }
-            len = 0;
-            in_regs = true;
-            for (int i = 0; i < cnt; ++i) {
-                const int m = ms[i];
-                chain_walk<4>(col, w, gld(rp, m), gld(rp, m + 1), [&](int c, double x) {
-                    const int b = S.u.a.agg[c];
-                    bool found = b == a;  // inside the aggregate: dropped
-#pragma unroll
-                    for (int q = 0; q < kChainSlots; ++q) {
-                        const bool here = rb[q] == b;
-                        rw[q] = here ? rw[q] + x : rw[q];
-                        found = found || here;
-                    }
-#pragma unroll
-                    for (int q = 0; q < kChainSlots; ++q) {
-                        const bool here = !found && q == len;
-                        rb[q] = here ? b : rb[q];
-                        rw[q] = here ? x : rw[q];
-                    }
-                    len += found ? 0 : 1;
-                });
-            }
-            if (len <= kChainSlots) {
-                // odd-even transposition sort by column (unused slots last)
-#pragma unroll
-                for (int pass = 0; pass < kChainSlots; ++pass) {
-#pragma unroll
-                    for (int q = pass & 1; q + 1 < kChainSlots; q += 2) {
-                        const bool swap = rb[q] > rb[q + 1];
-                        const int tb = rb[q];
-                        const double tw = rw[q];
-                        rb[q] = swap ? rb[q + 1] : tb;
-                        rb[q + 1] = swap ? tb : rb[q + 1];
-                        rw[q] = swap ? rw[q + 1] : tw;
-                        rw[q + 1] = swap ? tw : rw[q + 1];
-                    }
-                }
-                if (!once) {
-#pragma unroll
-                    for (int q = 0; q < kChainSlots; ++q) {
-                        if (q < len) {
-                            gst(mb, q, (int32_t)rb[q]);
-                            gst(mw, q, rw[q]);
-                        }
-                    }
-                }
-            } else {
-                // more columns than slots: the row is formed again from its
-                // first entry, in the scratch
-                in_regs = false;
-                len = 0;
-                for (int i = 0; i < cnt; ++i) {
-                    const int m = ms[i];
-                    const int e1 = gld(rp, m + 1);
-                    for (int e = gld(rp, m); e < e1; ++e) {
-                        const int b = S.u.a.agg[gld(col, e)];
-                        const double x = gld(w, e);
-                        if (b == a) continue;
-                        int q = 0;
-                        while (q < len && mb[q] != b) ++q;
-                        if (q == len) {
-                            mb[len] = b;
-                            mw[len] = x;
-                            ++len;
-                        } else {
-                            mw[q] += x;
-                        }
-                    }
-                }
-                for (int i = 1; i < len; ++i) {
-                    const int b = mb[i];
-                    const double x = mw[i];
-                    int j = i - 1;
-                    while (j >= 0 && mb[j] > b) {
-                        mb[j + 1] = mb[j];
-                        mw[j + 1] = mw[j];
-                        --j;
-                    }
-                    mb[j + 1] = b;
-                    mw[j + 1] = x;
-                }
-            }
-            S.l.rcount[a] = len;
-        }
+        // ---- Galerkin: every fine entry is a contribution to a coarse row,
+        // in a slot of its row's (a multiple of four of them).  A slot's key
+        // orders the row by coarse column, then fine CSR order (the members'
+        // entries ascend with the members), so a slot's place is the number
+        // of smaller keys in its row; the first slot of each column then adds
+        // the column's contributions in that order.  A slot per thread, a
+        // tile of rows at a time.  Bound by the LDS reads and compares of the
+        // ranks (of one CU).  One thread per coarse row, matching each entry
+        // against 12 register slots, left most lanes idle behind the longest
+        // row: the levels from 992 vertices (3842 entries) on took 199 us in
+        // all, from 6016 414 and from 7500 (75000) 700, now 91, 254 and 358.
+        int nnzc = 0;
         __syncthreads();
-        // row pointers, in memory and in place of the lengths' scratch use
-        const int64_t nnzc = chain_scan(
-            nc, sh, [&](int a) { return S.l.rcount[a]; },
-            [&](int a, int q) {
-                gst(rpc, a, (int32_t)q);
-                S.p.afill[a] = q;
-            });
-        if (tid == 0) rpc[nc] = (int32_t)nnzc;
-        for (int a = tid; a < nc; a += T) {
-            const int base = S.p.afill[a];
-            if (once && in_regs) {
+        for (int a0 = 0; a0 < nc;) {
+            const int s0 = S.r.soff[a0];
+            int a1 = nc;
+            if (S.r.soff[nc] - s0 > kChainTile) {
+                int lo = a0 + 1;  // a row always fits
+                while (a1 - lo > 1) {
+                    const int mid = (lo + a1) >> 1;
+                    if (S.r.soff[mid] - s0 <= kChainTile) lo = mid;
+                    else a1 = mid;
+                }
+                a1 = lo;
+            }
+            const int cnt = S.r.soff[a1] - s0;
+            for (int i = tid; i < cnt; i += T) R.key[i] = 0xffffffffu;
+            __syncthreads();
+            for (int v = tid; v < n; v += T) {
+                const int a = S.u.a.agg[v];
+                if (a < a0 || a >= a1) continue;
+                const int base = S.r.soff[a] - s0 + S.p.off[v];
+                const int e0 = gld(rp, v), e1 = gld(rp, v + 1);
+                for (int e = e0; e < e1; e += 8) {
+                    int c[8];
 #pragma unroll
-                for (int q = 0; q < kChainSlots; ++q) {
-                    if (q < len) {
-                        gst(colc, base + q, (int32_t)rb[q]);
-                        gst(wc, base + q, rw[q]);
+                    for (int q = 0; q < 8; ++q) c[q] = gld(col, min(e + q, e1 - 1));
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        if (e + q < e1) {
+                            const uint32_t b = S.u.a.agg[c[q]];
+                            R.key[base + (e - e0) + q] =
+                                ((int)b == a ? kChainDrop : b << 19) | (uint32_t)(e + q);
+                            R.row[base + (e - e0) + q] = (uint16_t)a;
+                        }
                     }
                 }
-                continue;
             }
-            const int32_t* mb = J.mb + S.r.soff[a];
-            const double* mw = J.mw + S.r.soff[a];
-            const int l = S.l.rcount[a];
-            for (int q = 0; q < l; ++q) {
-                gst(colc, base + q, gld(mb, q));
-                gst(wc, base + q, gld(mw, q));
+            __syncthreads();
+            uint32_t key[kChainTile / kChainThreads];
+            int to[kChainTile / kChainThreads];
+#pragma unroll
+            for (int q = 0; q < kChainTile / kChainThreads; ++q) {
+                const int i = tid + q * kChainThreads;
+                to[q] = -1;
+                if (i < cnt) {
+                    key[q] = R.key[i];
+                    if (key[q] != 0xffffffffu) {
+                        const int a = R.row[i];
+                        const int lo = S.r.soff[a] - s0, hi = S.r.soff[a + 1] - s0;
+                        int less = 0;
+#pragma unroll 2
+                        for (int t = lo; t < hi; t += 4) {
+                            const uint4 x = *(const uint4*)&R.key[t];
+                            less += (x.x < key[q]) + (x.y < key[q]) + (x.z < key[q]) + (x.w < key[q]);
+                        }
+                        to[q] = lo + less;
+                    }
+                }
             }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kChainTile / kChainThreads; ++q)
+                if (to[q] >= 0) R.key[to[q]] = key[q];
+            __syncthreads();
+            // the slots that open a coarse entry, numbered in slot order:
+            // 64 slots of a wavefront by their ballot, the wavefronts' runs
+            // by a scan of their counts
+            uint32_t opens = 0, starts = 0;  // this thread's slots: a coarse entry, a row
+#pragma unroll
+            for (int q = 0; q < kChainTile / kChainThreads; ++q) {
+                if (q * kChainThreads >= cnt) break;
+                const int i = tid + q * kChainThreads;
+                const int t = min(i, cnt - 1), t1 = max(t - 1, 0);
+                const uint32_t x = R.key[t], x1 = R.key[t1];
+                const int a = R.row[t], a_1 = R.row[t1];
+                const bool real = i < cnt && x != 0xffffffffu;
+                const bool open = real && x < kChainDrop && (i == 0 || (x >> 19) != (x1 >> 19) || a != a_1);
+                starts |= real && t == S.r.soff[real ? a : a0] - s0 ? 1u << q : 0u;
+                opens |= open ? 1u << q : 0u;
+                const int c = __popcll(__ballot(open));
+                if ((tid & 63) == 0) runs[q * (kChainThreads / 64) + (tid >> 6)] = c;
+            }
+            __syncthreads();
+            const int nruns = (cnt + kChainThreads - 1) / kChainThreads * (kChainThreads / 64);
+            const int heads = chain_scan(
+                nruns, sh, [&](int i) { return runs[i]; }, [&](int i, int q) { runs[i] = q; });
+#pragma unroll
+            for (int q = 0; q < kChainTile / kChainThreads; ++q) {
+                if (q * kChainThreads >= cnt) break;
+                const int i = tid + q * kChainThreads;
+                const bool open = (opens >> q) & 1;
+                const int at = runs[q * (kChainThreads / 64) + (tid >> 6)] +
+                               __popcll(__ballot(open) & ((1ull << (tid & 63)) - 1));
+                if ((starts >> q) & 1) gst(rpc, (int)R.row[i], (int32_t)(nnzc + at));
+                if (open) R.head[at] = (uint16_t)i;
+            }
+            __syncthreads();
+            for (int q = tid; q < heads; q += T) {
+                const int i = R.head[q];
+                const uint32_t x = R.key[i];
+                const int a = R.row[i];
+                auto mine = [&](int t) { return t < cnt && (R.key[t] >> 19) == (x >> 19) && R.row[t] == a; };
+                // most columns have at most four contributions: in flight together
+                int m = 1;
+                double y[4];
+                y[0] = gld(w, (int)(x & 0x7ffffu));
+#pragma unroll
+                for (int t = 1; t < 4; ++t) {
+                    if (m == t && mine(i + t)) m = t + 1;
+                    y[t] = gld(w, (int)(R.key[i + (t < m ? t : 0)] & 0x7ffffu));
+                }
+                double sum = y[0];
+#pragma unroll
+                for (int t = 1; t < 4; ++t) sum = t < m ? sum + y[t] : sum;
+                if (m == 4)
+                    for (int t = i + 4; mine(t); ++t) sum += gld(w, (int)(R.key[t] & 0x7ffffu));
+                gst(colc, nnzc + q, (int32_t)(x >> 19));
+                gst(wc, nnzc + q, sum);
+            }
+            nnzc += heads;
+            a0 = a1;
+            __syncthreads();
         }
+        if (tid == 0) rpc[nc] = nnzc;
         if (tid == 0) J.hdr[k] = hd;
         cur_rp_off = i32_used + n;
         cur_cw_off = cw_used;

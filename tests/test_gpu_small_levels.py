@@ -1,7 +1,7 @@
 """GPU: the kernels that keep a small level in one workgroup, at the edges of
 their ranges, against the oracle: dense levels (tiles of 16), register rows
-with weights that single precision cannot hold, and small levels of several
-eigenpairs.
+with weights that single precision cannot hold, small levels of several
+eigenpairs, and their setup (integers and weights bit for bit).
 
 Tolerances: those of the FP64 parity tests (tests/gpu_compare.py); a dense
 level's blocks of 16 steps and the block's reciprocal square roots round as
@@ -9,7 +9,7 @@ often as the plain steps do, so they apply as they are."""
 import numpy as np
 import pytest
 
-from gpu_compare import COS_TOL, LAM_RTOL, oracle_of, run_gpu, say
+from gpu_compare import COS_TOL, LAM_RTOL, assert_hierarchy_equal, oracle_of, run_gpu, say
 from paper_1412_0565_amd import graphs as G
 
 pytestmark = pytest.mark.gpu
@@ -82,3 +82,18 @@ def test_block_levels(name, p):
         assert float(X[:, c] @ ref.X[:, c]) / (np.linalg.norm(X[:, c]) * np.linalg.norm(ref.X[:, c])) >= 1 - COS_TOL
         assert abs(lams[c] - ref.lams[c]) <= LAM_RTOL * ref.lams[c]
     assert np.allclose(X.T @ X, np.eye(p), atol=1e-11)
+
+
+# one slot tile or many (13312 slots), rows of a few entries or near the
+# longest, members of one aggregate only
+@pytest.mark.parametrize("real", [False, True])
+@pytest.mark.parametrize("name", ["path26", "cycle27", "grid8x4", "grid64x128", "rgg1300", "rgg8000", "er300", "er8000"])
+def test_small_level_setup(name, real):
+    g = {"path26": lambda: G.path(26), "cycle27": lambda: G.cycle(27), "grid8x4": lambda: G.grid2d(8, 4),
+         "grid64x128": lambda: G.grid2d(64, 128), "rgg1300": lambda: G.rgg(1300, 10.0, seed=2),
+         "rgg8000": lambda: G.rgg(8000, 11.0, seed=3), "er300": lambda: G.erdos_renyi_connected(300, 0.03, seed=4),
+         "er8000": lambda: G.erdos_renyi_connected(8000, 0.00105, seed=5)}[name]()
+    g = _real(g) if real else g
+    _, _, _, levels, arrays = run_gpu(g)
+    say(f"[setup] {name} real={real} {[(L.n, L.nnz) for L in levels]}")
+    assert_hierarchy_equal(g, oracle_of(g), levels, arrays, exact_g=False)
