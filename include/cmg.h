@@ -111,8 +111,8 @@ typedef struct {
                                     are reproducible within a process but may differ (within
                                     rounding) between processes.  0 (default): fixed rules. */
     int32_t block_regs;          /* levels refined inside one workgroup: 0 (default) holds a level
-                                    of at most 64 vertices (most of up to 128) as a dense matrix
-                                    and takes sixteen PI steps per product with its sixteenth
+                                    of at most 64 vertices (most of up to 128, nearly full ones
+                                    of up to 176) as a dense matrix and takes sixteen PI steps per product with its sixteenth
                                     power, a larger one's rows in registers for all its steps
                                     where a layout fits (rows of at most 128 entries, those
                                     beyond the layout's slots in an LDS list); -1 always reads

@@ -322,6 +322,8 @@ hipError_t launch_step_pi(const StepJob* job, int nblocks, int kind, hipStream_t
 constexpr int kStepBlock = 512;
 
 constexpr int kGridBlock = 512;
+// rows + entries of a merge-path workgroup that the products of a jump hold in registers
+constexpr int kMergeHeld = 12 * kGridBlock;
 constexpr int kBlockKernelThreads = 1024;
 constexpr int kBlockRegsThreads = 512;   // 256 VGPRs per lane for register rows
 constexpr int kBlockLdsMax = 144 * 1024;  // LDS image budget of the single-workgroup kernel

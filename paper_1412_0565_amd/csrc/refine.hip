@@ -985,6 +985,175 @@ __device__ __forceinline__ void drive_merge(const int32_t* __restrict__ rp, int 
     }
 }
 
+// ---- merge path, a workgroup's share held in registers
+//
+// A jump multiplies by the same matrix some 60 to 400 times.  Where a
+// workgroup's share is at most kMergeHeld items and kMergeRegRows rows,
+// every thread keeps the columns and weights of its own items, and the
+// rows' vector values and sums stay in LDS, so a product is one batch of
+// gathers, the walk, the scan and the rows' update; nothing but the vector
+// is read from memory.  Bound by those latencies (7 us at 4000 items) and
+// the grid barrier (8 us at 200 workgroups).  drive_merge reads everything
+// again behind the barrier, which invalidates the L2: 28700 rows of 759000
+// entries took 24 us a product, this way 15.5.  Shares for more workgroups
+// than CUs were slower: two on one CU take twice as long as the others.
+constexpr int kMergeRegIPT = kMergeHeld / kGridBlock;
+constexpr int kMergeRowsPer = 3;  // own rows per thread
+constexpr int kMergeRegRows = kMergeRowsPer * kGridBlock;
+static_assert(2 * kMergeRegRows <= kMergeChunk, "both in MergeShared::sw; the others half as long each");
+
+template <int WK>
+struct MergeRegs {
+    using W = std::conditional_t<WK == kWNative, double, float>;  // exact for every other storage
+    int c[kMergeRegIPT];   // columns of the items that are entries
+    W w[kMergeRegIPT];
+    uint32_t ents, ends;   // items that are entries / row ends
+    int row0, row;         // first row, and the row after the last item (of the workgroup's)
+};
+
+// False (in every thread) where the share is larger.
+template <int WK>
+__device__ __forceinline__ bool merge_regs_load(const LevelDev& L, int r0, int r1, const double* win, MergeRegs<WK>& m,
+                                                MergeShared& sh) {
+    const int tid = (int)threadIdx.x;
+    const int e0 = gld(L.rp, r0);
+    const int nrows = r1 - r0;
+    const int nent = gld(L.rp, r1) - e0;
+    const int total = nrows + nent;
+    if (total > kMergeHeld || nrows > kMergeRegRows || nrows < 1) return false;
+    const auto wv = weights_of<double, WK>(L);
+    const int diag = min(tid * kMergeRegIPT, total);
+    int lo = max(0, diag - nent), hi = min(nrows, diag);
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (gld(L.rp, r0 + mid + 1) - e0 <= diag - mid - 1) lo = mid + 1;
+        else hi = mid;
+    }
+    int i = lo, e = e0 + diag - lo;
+    m.row0 = i;
+    m.ents = m.ends = 0;
+    int end = i < nrows ? gld(L.rp, r0 + i + 1) : e;
+#pragma unroll
+    for (int q = 0; q < kMergeRegIPT; ++q) {
+        m.c[q] = r0;  // a vector value that is there; the item drops it
+        m.w[q] = 0;
+        if (diag + q >= total) continue;
+        if (e < end) {
+            m.ents |= 1u << q;
+            m.c[q] = gld(L.col, e);
+            m.w[q] = (typename MergeRegs<WK>::W)wv[e];
+            ++e;
+        } else {
+            m.ends |= 1u << q;
+            ++i;
+            if (i < nrows) end = gld(L.rp, r0 + i + 1);
+        }
+    }
+    m.row = i;
+#pragma unroll
+    for (int t = 0; t < kMergeRowsPer; ++t) {
+        const int r = tid + t * kGridBlock;
+        if (r < nrows) sh.sw[r] = gld(win, r0 + r);
+    }
+    __syncthreads();
+    return true;
+}
+
+// Product of a jump (as JumpOp with drive_merge): y = T_{j+1} to op.wout.
+template <int WK>
+__device__ __forceinline__ void merge_regs_product(JumpOp<WK>& op, int r0, int nrows, bool last, MergeRegs<WK>& m,
+                                                   MergeShared& sh) {
+    const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    // own rows: T_j, the sums of the entries, T_{j-1} and the jump's sum (the
+    // grid barrier before each product orders them)
+    double* rx = sh.sw;
+    double* rs = sh.sw + kMergeRegRows;
+    double* rz = (double*)sh.win;
+    double* rj = (double*)sh.scol;
+    double y[kMergeRegIPT];
+#pragma unroll
+    for (int q = 0; q < kMergeRegIPT; ++q) y[q] = op.xk(m.c[q]);
+    int i = m.row0, frow = -1;
+    double part = 0.0, fpart = 0.0;
+    double x = i < nrows ? rx[i] : 0.0;
+#pragma unroll
+    for (int q = 0; q < kMergeRegIPT; ++q) {
+        if ((m.ents >> q) & 1) part += op.term(y[q], (double)m.w[q], x);
+        if ((m.ends >> q) & 1) {
+            if (frow < 0) {
+                frow = i;
+                fpart = part;
+            } else {
+                rs[i] = part;
+            }
+            part = 0.0;
+            ++i;
+            x = i < nrows ? rx[i] : 0.0;
+        }
+    }
+    // inclusive segmented scan of the carries (rows are non-decreasing in tid)
+    const int myrow = m.row;
+    double v = part;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int ro = __shfl_up(myrow, o, 64);
+        const double vo = __shfl_up(v, o, 64);
+        if (lane >= o && ro == myrow) v += vo;
+    }
+    const int first = __shfl(myrow, 0, 64);
+    if (lane == 63) {
+        sh.wrow[wv] = myrow;
+        sh.wtail[wv] = v;
+        sh.wfirst[wv] = first;
+    }
+    __syncthreads();
+    // what the wavefronts before carry into this one
+    int crow = -1;
+    double cval = 0.0;
+#pragma unroll
+    for (int w = 0; w < kGridBlock / 64; ++w) {
+        const int rw = sh.wrow[w];
+        const double tail = sh.wtail[w] + (sh.wfirst[w] == rw && crow == rw ? cval : 0.0);
+        if (w < wv) {
+            crow = rw;
+            cval = tail;
+        }
+    }
+    if (myrow == first && myrow == crow) v += cval;
+    int prow = __shfl_up(myrow, 1, 64);
+    double pval = __shfl_up(v, 1, 64);
+    if (lane == 0) {
+        prow = crow;
+        pval = cval;
+    }
+    if (frow >= 0) rs[frow] = fpart + (prow == frow ? pval : 0.0);
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < kMergeRowsPer; ++t) {
+        const int r = tid + t * kGridBlock;
+        if (r >= nrows) continue;
+        const double xr = rx[r], s = rs[r];
+        double yr, sum;
+        if (op.first) {
+            yr = xr + op.be * s;
+            sum = xr;
+            gst(op.jback, r0 + r, xr);
+        } else {
+            yr = 2.0 * xr + op.be * s - rz[r];
+            sum = rj[r];
+        }
+        gst(op.wout, r0 + r, yr);
+        sum += op.cj * yr;
+        if (last) gst(op.jsum, r0 + r, sum);
+        rj[r] = sum;
+        rz[r] = xr;
+        rx[r] = yr;
+        op.acc[0] += xr * yr;
+        op.acc[1] += yr * yr;
+        op.acc[2] += xr * xr;
+    }
+}
+
 // TRAV = 0: merge path; TRAV = G > 0: G lanes per row.
 template <int TRAV, class Op>
 __device__ __forceinline__ void drive(const LevelDev& L, int r0, int r1, Op& op, MergeShared* sh, double* red) {
@@ -1026,6 +1195,9 @@ __device__ __forceinline__ bool jump_products_run(const LevelDev& L, GridCtx& c,
     double cj = 2.0 * (double)K / (double)(K + 1);
     double* bufs[2] = {(double*)L.buf0, (double*)L.buf1};
     const double be1 = 2.0 / L.g;
+    MergeRegs<WK> mr;
+    bool held = false;
+    if constexpr (TRAV == 0) held = merge_regs_load<WK>(L, r0, r1, bufs[cur], mr, *sh);
     for (int j = 0; j < d; ++j) {
         double acc[3];
         if (TRAV > 0 && staged) {
@@ -1060,7 +1232,8 @@ __device__ __forceinline__ bool jump_products_run(const LevelDev& L, GridCtx& c,
             op.cj = cj;
             op.acc[0] = op.acc[1] = op.acc[2] = 0.0;
             if constexpr (TRAV == 0) {
-                drive_merge(L.rp, r0, r1, op, *sh);
+                if (held) merge_regs_product<WK>(op, r0, r1 - r0, j == d - 1, mr, *sh);
+                else drive_merge(L.rp, r0, r1, op, *sh);
             } else if (L.ileave) {
                 const int cw = 4 * ((int)blockDim.x / TRAV);
                 for (int a = x0 + xp * cw; a < x1; a += np * cw)

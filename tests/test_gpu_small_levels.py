@@ -84,6 +84,28 @@ def test_block_levels(name, p):
     assert np.allclose(X.T @ X, np.eye(p), atol=1e-11)
 
 
+# shares of the merge path that a jump holds in registers, at hub rows that
+# leave one share too large (5000 entries and 1800 of other rows against 6144) and at real weights
+@pytest.mark.parametrize("real", [False, True])
+@pytest.mark.parametrize("hub", [0, 2000, 5000])
+def test_held_merge_products(hub, real):
+    g = G.chung_lu(20000, 2.5, 8.0, 400.0, seed=3, int_weights=True)
+    row = np.repeat(np.arange(g.n), np.diff(g.row_ptr))
+    up = row < g.col
+    far = np.arange(1, g.n, max(1, g.n // hub))[:hub] if hub else np.arange(0)
+    u, v = np.concatenate([row[up], np.zeros(len(far), int)]), np.concatenate([g.col[up], far])
+    _, at = np.unique(u.astype(np.int64) * g.n + v, return_index=True)
+    g = G.from_edges(g.n, u[at], v[at])
+    g = _real(g) if real else g
+    ref = oracle_of(g)
+    lam, x, _, levels, _ = run_gpu(g, spmv_variant=2, block_rows=1)
+    say(f"[merge] hub={hub} real={real} steps {[L.k for L in levels]} oracle {[L.k for L in ref.levels]}")
+    assert [L.k for L in levels] == [L.k for L in ref.levels]
+    assert max(L.k for L in levels) >= 130  # a jump
+    assert abs(float(x @ ref.y)) / (np.linalg.norm(x) * np.linalg.norm(ref.y)) >= 1 - COS_TOL
+    assert abs(lam - ref.lam) <= LAM_RTOL * ref.lam
+
+
 # one slot tile or many (13312 slots), rows of a few entries or near the
 # longest, members of one aggregate only
 @pytest.mark.parametrize("real", [False, True])
